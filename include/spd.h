@@ -218,7 +218,8 @@ spd_status spd_sync(spd_handle* h, spd_step_result* last);
 /* Debug and parity reads (synchronous; host destination). what:
  *   SPD_DBG_RESID:       n*d fp32, in-flight residual streams; position q lives in row q mod n
  *   SPD_DBG_ANCHORS:     n*n*d fp32, [row q mod n][anchor j][d], anchor j = H^{beta_j}
- *   SPD_DBG_PDM_HIDDEN:  8*d fp32, the PDM's output rows of the last step (row i = position c+i)
+ *   SPD_DBG_PDM_HIDDEN:  8*d fp32, the PDM's output rows of the last step (row i = position c+i;
+ *                        rows past the step's a keep what earlier steps left, zeros at first)
  *   SPD_DBG_EXIT_LOGITS: V fp32, target logits of the last exiting token (needs spd_set_debug)
  *   SPD_DBG_PDM_LOGITS:  V fp32, the PDM's logits of the last step (needs spd_set_debug)
  *   SPD_DBG_TOKENS:      max_tokens int32, token id per position

@@ -13,6 +13,7 @@
 
 #include "spd.h"
 #include "spd_dev.h"
+#include "spd_prefill.h"
 
 using namespace spd;
 
@@ -26,6 +27,8 @@ struct Layout {
   size_t kv, pkv, pt, rope, state, tok, forced, log, resid, anch, pdmx, pfx, pfanch, dbg, lay;
   size_t q[2], ao[2], act[2], part[2], cnt[2], hkey[2], rpart[2], rtick[2];
   size_t ktrace;
+  size_t pfpx, pfq, pfpart, pfrs, pfpa, pfpb, pfzero;  // prefill of bf16 models
+  int pf_rows;
   size_t su, swlog, swgmax, sqids, sqp, sqcnt, spq;  // sampled decoding
   size_t total;
   int wlog_stride;
@@ -121,8 +124,20 @@ Layout make_layout(const spd_config& c) {
   L.resid = take(sizeof(float) * n * d);
   L.anch = take(sizeof(float) * n * n * d);
   L.pdmx = take(sizeof(float) * kMaxRows * d);
-  L.pfx = take(sizeof(float) * kMaxRows * d);
-  L.pfanch = take(sizeof(float) * kMaxRows * n * d);
+  if (c.dtype == SPD_BF16) {  // chunks on matrix cores
+    const size_t R = L.pf_rows = prefill_rows(c.max_tokens);
+    L.pfx = take(sizeof(float) * R * d);
+    L.pfpx = take(sizeof(float) * R * d);
+    L.pfq = take(sizeof(float) * R * qdim);
+    L.pfpart = take(sizeof(float) * prefill_part_floats(R, d, c.ffn_dim, qdim + 2 * hkv * dh));
+    L.pfrs = take(sizeof(float) * R);
+    L.pfpa = take(sizeof(uint16_t) * 3 * R * std::max(d, qdim));
+    L.pfpb = take(sizeof(uint16_t) * 3 * R * std::max(d, c.ffn_dim));
+    L.pfzero = take(256);
+  } else {  // 8-row chunks
+    L.pfx = take(sizeof(float) * kMaxRows * d);
+    L.pfanch = take(sizeof(float) * kMaxRows * n * d);
+  }
   L.dbg = take(sizeof(float) * 2 * (size_t)c.vocab);
   L.lay = take(sizeof(LayerDesc) * (c.n_layers + c.pdm_layers));
   const size_t part_floats = (size_t)64 * hkv * L.max_splits * (dh + 2);
@@ -167,6 +182,7 @@ struct spd_handle {
   spd_config cfg;
   Layout lay;
   Ctx ctx;
+  PrefillBufs pf = {};  // bf16 models
   int dev = 0;
   int bf16 = 0;
   int J = 0;  // layer slots per step = longest stage
@@ -423,8 +439,28 @@ static spd_status enqueue_step(spd_handle* h, int forced_override) {
   return launch_check(h, "step");
 }
 
+// The prompt's last row through the LM head: the argmax key (or, sampled, the draw) the reseed reads.
 template <typename WT>
-static spd_status enqueue_prefill(spd_handle* h, int len) {
+static void enqueue_first_token(spd_handle* h, int row, int len) {
+  const Ctx& C = h->ctx;
+  if (C.sam.top_k > 0)  // the first token is drawn from the top-k distribution
+    Launch<WT>::head_sample(C, 2, row, len, -1, 0, h->main);
+  else
+    Launch<WT>::head(C, 2, row, h->main);
+}
+
+// bf16 models: chunks of up to kPrefillRows rows on matrix cores.
+static spd_status enqueue_prefill_bf16(spd_handle* h, int len) {
+  int row = 0;
+  prefill_mfma(h->ctx, h->pf, h->layer_desc.data(), len, h->main, &row);
+  enqueue_first_token<uint16_t>(h, row, len);
+  launch_reseed(h->ctx, len, -1, len, h->main, 1);
+  return launch_check(h, "prefill");
+}
+
+// fp32 models: 8-row chunks through the row GEMVs (an fp32 weight has no exact bf16 form).
+static spd_status enqueue_prefill_f32(spd_handle* h, int len) {
+  using WT = float;
   const Ctx& C = h->ctx;
   const int n = h->cfg.n_stages, L = h->cfg.n_layers;
   for (int t0 = 0; t0 < len; t0 += kMaxRows) {
@@ -440,16 +476,11 @@ static spd_status enqueue_prefill(spd_handle* h, int len) {
     Launch<WT>::pdm_fc(C, 1, rc, h->main);
     for (int i = 0; i < h->cfg.pdm_layers; i++)
       Launch<WT>::rows_layer(C, rows_block(L + i, rc, t0, C.pdm_x, nullptr, -1, 1), kMaxRows, 0, h->main);
-    if (t0 + rc == len) {
-      if (C.sam.top_k > 0)  // the first token is drawn from the top-k distribution
-        Launch<WT>::head_sample(C, 2, rc - 1, len, -1, 0, h->main);
-      else
-        Launch<WT>::head(C, 2, rc - 1, h->main);
-    }
+    if (t0 + rc == len) enqueue_first_token<WT>(h, rc - 1, len);
     spd_status st = launch_check(h, "prefill");
     if (st != SPD_OK) return st;
   }
-  launch_reseed(C, len, -1, len, h->main, h->bf16);
+  launch_reseed(C, len, -1, len, h->main, 0);
   return launch_check(h, "prefill reseed");
 }
 
@@ -613,7 +644,21 @@ spd_status spd_init(const spd_config* cfg, const spd_weights* w, void* workspace
   C.anchors = (float*)(ws + lay.anch);
   C.pdm_x = (float*)(ws + lay.pdmx);
   C.pf_x = (float*)(ws + lay.pfx);
-  C.pf_anch = (float*)(ws + lay.pfanch);
+  if (h->bf16) {
+    PrefillBufs& P = h->pf;
+    P.rows = lay.pf_rows;
+    P.part_cap = prefill_part_floats(P.rows, c.d_model, c.ffn_dim, C.qdim + 2 * C.kvdim);
+    P.x = C.pf_x;
+    P.px = (float*)(ws + lay.pfpx);
+    P.q = (float*)(ws + lay.pfq);
+    P.part = (float*)(ws + lay.pfpart);
+    P.rs = (float*)(ws + lay.pfrs);
+    P.pa = (uint16_t*)(ws + lay.pfpa);
+    P.pb = (uint16_t*)(ws + lay.pfpb);
+    P.zeros = (uint16_t*)(ws + lay.pfzero);
+  } else {
+    C.pf_anch = (float*)(ws + lay.pfanch);
+  }
   C.dbg_logits = (float*)(ws + lay.dbg);
   C.debug = 0;
   for (int s = 0; s < 2; s++) {
@@ -686,6 +731,8 @@ spd_status spd_init(const spd_config* cfg, const spd_weights* w, void* workspace
   HIPI(hipMemcpyAsync(ws + lay.pt, h->page_table.data(), sizeof(int32_t) * lay.num_pages, hipMemcpyHostToDevice,
                       h->main));
   HIPI(hipMemsetAsync(ws + lay.state, 0, sizeof(DevState), h->main));
+  HIPI(hipMemsetAsync(ws + lay.pdmx, 0, sizeof(float) * kMaxRows * c.d_model, h->main));
+  if (h->bf16) HIPI(hipMemsetAsync(ws + lay.pfzero, 0, 256, h->main));
   HIPI(hipMemsetAsync(ws + lay.tok, 0, sizeof(int32_t) * (c.max_tokens + 8), h->main));
   HIPI(hipMemsetAsync(ws + lay.forced, 0xff, sizeof(int32_t) * (c.max_tokens + 8), h->main));
   for (int s = 0; s < 2; s++) HIPI(hipMemsetAsync(ws + lay.cnt[s], 0, sizeof(int32_t) * kMaxStages * c.n_kv_heads, h->main));
@@ -851,7 +898,7 @@ spd_status spd_prefill(spd_handle* h, const int32_t* prompt, int32_t len, int32_
     if (prompt[i] < 0 || prompt[i] >= h->cfg.vocab) return SPD_E_INVAL;
   HIPC(hipSetDevice(h->dev));
   HIPC(hipMemcpyAsync(h->ctx.tok, prompt, sizeof(int32_t) * len, hipMemcpyHostToDevice, h->main));
-  spd_status st = h->bf16 ? enqueue_prefill<uint16_t>(h, len) : enqueue_prefill<float>(h, len);
+  spd_status st = h->bf16 ? enqueue_prefill_bf16(h, len) : enqueue_prefill_f32(h, len);
   if (st != SPD_OK) return st;
   int32_t y = 0;
   HIPC(hipMemcpyAsync(&h->pinned[0].target_argmax, &h->ctx.st->y, sizeof(int32_t), hipMemcpyDeviceToHost, h->main));

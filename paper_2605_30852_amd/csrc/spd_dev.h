@@ -126,8 +126,8 @@ struct Ctx {
   float* resid;     // [n][d] in-flight residual streams, row q mod n
   float* anchors;   // [n][n][d] row q mod n, anchor j
   float* pdm_x;     // [8][d] PDM residual rows
-  float* pf_x;      // [8][d] prefill chunk residual rows
-  float* pf_anch;   // [8][n][d] prefill chunk anchors
+  float* pf_x;      // prefill chunk residual rows: [8][d] (fp32 models), [kPrefillRows][d] at most (bf16)
+  float* pf_anch;   // [8][n][d] prefill chunk anchors (fp32 models)
   float* dbg_logits;// [2][V]
   int debug;
   BufSet b[2];      // 0: target stream, 1: PDM stream

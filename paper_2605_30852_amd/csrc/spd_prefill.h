@@ -1,0 +1,41 @@
+// Prefill of bf16 models in chunks of up to kPrefillRows prompt rows: the launchers of spd_prefill.hip
+// and the scratch they use. Internal; not part of the C ABI.
+#pragma once
+#include "spd_dev.h"
+
+namespace spd {
+
+// Prompt rows of one chunk. Every layer's weights are read once per chunk, and 2048 rows give the
+// narrow projections (N = d) enough 128 x 128 tiles for 256 CUs; more rows would only add scratch.
+constexpr int kPrefillRows = 2048;
+constexpr int kPrefillMaxSplit = 16;  // K splits of one projection
+
+// An fp32 activation matrix [rows][K] as three bf16 planes whose sum is the fp32 value exactly:
+// element (p, m, k) at p + p * stride + m * K + k.
+struct Planes {
+  uint16_t* p;
+  size_t stride;
+};
+
+// Scratch of the prefill (in the workspace).
+struct PrefillBufs {
+  int rows;          // row capacity, a multiple of 128
+  size_t part_cap;   // floats in part
+  float* x;          // [rows][d] residual rows of the target
+  float* px;         // [rows][d] residual rows of the draft module
+  float* q;          // [rows][Hq*dh] rotated queries
+  float* part;       // K-split partial sums, [split][row][column]
+  float* rs;         // [rows] 1 / rms of the normalised rows
+  uint16_t* pa;      // planes of [rows][max(d, Hq*dh)]: normalised rows, attention outputs
+  uint16_t* pb;      // planes of [rows][max(d, F)]: SwiGLU activations, raw stage inputs
+  uint16_t* zeros;   // 256 bytes of zeros
+};
+
+int prefill_rows(int max_tokens);
+size_t prefill_part_floats(int rows, int d, int F, int qkv_cols);
+
+// The whole prompt: C.tok[0, len) through the target and the draft module's caches; the last row's
+// residual ends in row *last_row of B.x. Asynchronous on stream.
+void prefill_mfma(const Ctx& C, const PrefillBufs& B, const LayerDesc* layers, int len, void* stream, int* last_row);
+
+}  // namespace spd

@@ -1,0 +1,815 @@
+// Prefill of bf16 models on matrix cores.
+//
+// A chunk of prompt rows goes through a layer as four dense projections and one causal attention. The
+// activations stay fp32 in value: every fp32 operand x is cut into three bf16 planes by truncation,
+// hi + mid + lo == x exactly (24 significant bits in three groups of eight), and each product runs as
+// three bf16 MFMAs against the bf16 weights (or keys, or values), which are exact too. Only the order
+// of the sums differs from an fp32 GEMV. v_mfma_f32_32x32x16_bf16 moves 16 times the multiplies of the
+// fp32 instruction, so three of them are still five times faster.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+
+#include "spd_devfn.h"
+#include "spd_prefill.h"
+
+namespace spd {
+
+namespace {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef __attribute__((address_space(1))) const void gbytes;
+typedef __attribute__((address_space(3))) void lbytes;
+
+// x as bf16 bits hi, mid, lo with hi + mid + lo == x (the parts below the smallest bf16 excepted).
+// Truncation: no part overflows, and an infinity or NaN stays in hi alone.
+__device__ __forceinline__ void split3(float x, uint32_t& hi, uint32_t& mid, uint32_t& lo) {
+  const uint32_t u = __float_as_uint(x) & 0xffff0000u;
+  const bool fin = (u & 0x7f800000u) != 0x7f800000u;
+  const float r = fin ? x - __uint_as_float(u) : 0.f;
+  const uint32_t m = __float_as_uint(r) & 0xffff0000u;
+  hi = u >> 16;
+  // a NaN whose payload sits in the low half would read as an infinity
+  if (!fin && (__float_as_uint(x) & 0x7fffffu) != 0) hi |= 0x40u;
+  mid = m >> 16;
+  lo = __float_as_uint(r - __uint_as_float(m)) >> 16;
+}
+
+// Four consecutive elements into the three planes (8-byte aligned).
+__device__ __forceinline__ void store_planes4(const Planes& P, size_t at, float a, float b, float c, float d) {
+  uint32_t h[4], m[4], l[4];
+  split3(a, h[0], m[0], l[0]);
+  split3(b, h[1], m[1], l[1]);
+  split3(c, h[2], m[2], l[2]);
+  split3(d, h[3], m[3], l[3]);
+  *reinterpret_cast<uint2*>(P.p + at) = make_uint2(h[0] | h[1] << 16, h[2] | h[3] << 16);
+  *reinterpret_cast<uint2*>(P.p + P.stride + at) = make_uint2(m[0] | m[1] << 16, m[2] | m[3] << 16);
+  *reinterpret_cast<uint2*>(P.p + 2 * P.stride + at) = make_uint2(l[0] | l[1] << 16, l[2] | l[3] << 16);
+}
+
+// ------------------------------------------------------------------------------- residual and norm
+// One row per workgroup: v = x (or the token's embedding, or nothing) + the S partial sums of the
+// projection before it, in split order; v becomes x. With a gain, v * gain goes to the planes of the
+// next projection and 1 / rms(v) to rs; raw: v's own planes (the draft module's stage input).
+struct NormArgs {
+  float* x;
+  int d, S, base;        // base: 0 x, 1 the token's embedding, 2 zero
+  const float* part;     // [S][rows][d], row stride d
+  size_t part_stride;    // floats per split
+  const int32_t* tok;
+  const uint16_t* embed;
+  const float* gain;     // null: no norm
+  float eps;
+  Planes out, raw;       // raw.p null: none
+  float* rs;
+};
+
+constexpr int kNormVec = 8192 / 4 / kWG;  // float4 groups per thread at the largest d
+
+__global__ __launch_bounds__(kWG) void k_pf_norm(NormArgs A) {
+  __shared__ float red[4];
+  const int m = blockIdx.x, d = A.d, n4 = d >> 2;
+  float* x = A.x + (size_t)m * d;
+  const uint16_t* E = A.base == 1 ? A.embed + (size_t)A.tok[m] * d : nullptr;
+  float4 v[kNormVec];
+  float ss = 0.f;
+#pragma unroll
+  for (int i = 0; i < kNormVec; i++) {
+    const int k4 = threadIdx.x + i * kWG;
+    if (k4 >= n4) break;
+    float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (A.base == 0) {
+      t = *reinterpret_cast<const float4*>(x + k4 * 4);
+    } else if (A.base == 1) {
+      const uint2 e = *reinterpret_cast<const uint2*>(E + k4 * 4);
+      t = make_float4(bf_lo(e.x), bf_hi(e.x), bf_lo(e.y), bf_hi(e.y));
+    }
+    for (int s = 0; s < A.S; s++) {
+      const float4 p = *reinterpret_cast<const float4*>(A.part + s * A.part_stride + (size_t)m * d + k4 * 4);
+      t.x += p.x;
+      t.y += p.y;
+      t.z += p.z;
+      t.w += p.w;
+    }
+    ss = fmaf(t.x, t.x, ss);
+    ss = fmaf(t.y, t.y, ss);
+    ss = fmaf(t.z, t.z, ss);
+    ss = fmaf(t.w, t.w, ss);
+    v[i] = t;
+    *reinterpret_cast<float4*>(x + k4 * 4) = t;
+  }
+  if (A.gain == nullptr) return;
+#pragma unroll
+  for (int i = 0; i < kNormVec; i++) {
+    const int k4 = threadIdx.x + i * kWG;
+    if (k4 >= n4) break;
+    const float4 g = *reinterpret_cast<const float4*>(A.gain + k4 * 4);
+    const float4 t = v[i];
+    const size_t at = (size_t)m * d + k4 * 4;
+    store_planes4(A.out, at, t.x * g.x, t.y * g.y, t.z * g.z, t.w * g.w);
+    if (A.raw.p != nullptr) store_planes4(A.raw, at, t.x, t.y, t.z, t.w);
+  }
+  const float tot = block_sum(ss, red);
+  if (threadIdx.x == 0) A.rs[m] = 1.0f / sqrtf(tot / (float)d + A.eps);
+}
+
+// ------------------------------------------------------------------------------------- projections
+enum GemmKind { GK_PLAIN = 0, GK_QKV = 1, GK_GATEUP = 2 };
+
+// Where a pair's two columns go: QKV pairs are a head's RoPE partners (q to the query rows, k and v to
+// the paged cache), gate/up pairs the two factors of one SwiGLU activation.
+struct PairOut {
+  const float* rs;            // row scales
+  float* q;                   // QKV
+  uint16_t* kv;
+  const int32_t* page_table;
+  const float2* rope;
+  int pos0, hq, hkv, dh, page;
+  Planes act;                 // gate/up
+  int F;
+};
+
+__device__ __forceinline__ void qkv_store(const PairOut& O, int m, int q, float lo, float hi) {
+  const int half = O.dh >> 1, head = q / half, j = q - head * half, pos = O.pos0 + m;
+  if (head < O.hq + O.hkv) {  // q and k are rotated at the row's position
+    const float2 r = O.rope[(size_t)pos * half + j];
+    const float a = lo * r.x - hi * r.y, b = hi * r.x + lo * r.y;
+    lo = a;
+    hi = b;
+  }
+  if (head < O.hq) {
+    float* o = O.q + (size_t)m * O.hq * O.dh + head * O.dh;
+    o[j] = lo;
+    o[j + half] = hi;
+  } else {
+    const int is_v = head >= O.hq + O.hkv, hk = head - O.hq - (is_v ? O.hkv : 0);
+    const size_t off = ((size_t)O.page_table[pos / O.page] * 2 + is_v) * O.hkv * O.page * O.dh +
+                       ((size_t)hk * O.page + pos % O.page) * O.dh + j;
+    st1<uint16_t>(O.kv, off, lo);
+    st1<uint16_t>(O.kv, off + half, hi);
+  }
+}
+
+__device__ __forceinline__ void act_store(const PairOut& O, int m, int q, float g, float u) {
+  uint32_t h, mi, l;
+  split3(g / (1.0f + expf(-g)) * u, h, mi, l);
+  const size_t at = (size_t)m * O.F + q;
+  O.act.p[at] = (uint16_t)h;
+  O.act.p[O.act.stride + at] = (uint16_t)mi;
+  O.act.p[2 * O.act.stride + at] = (uint16_t)l;
+}
+
+struct GemmArgs {
+  Planes a;                       // [M][K]
+  const uint16_t *w0, *w1, *w2;   // plain: w0; QKV: wq, wk, wv; gate/up: wg, wu
+  const uint16_t* zeros;
+  int M, K, ldw;
+  int cols;                       // plain: columns; pair kinds: pairs (two columns each)
+  int KS;                         // K range of a split, a multiple of 64
+  int mt, nt;                     // tiles
+  float* part;                    // null: the pair epilogue
+  PairOut out;
+};
+
+// C = A W^T over a BM x BN tile: workgroup of four waves, each WM x WN in 32 x 32 MFMA tiles.
+// The three A planes and the W rows of a K step of BK go to LDS with direct 16-byte global loads
+// (double buffered; the 16-byte chunks of a row are permuted so that eight consecutive rows read eight
+// different bank groups). Pair kinds interleave the weights' rows by 32 so that a lane holds both
+// columns of its pairs in neighbouring MFMA tiles.
+//
+// Sums: a block of 64 inputs starts from zero and adds its lo products first, then mid, then hi, so
+// that only the 4 hi MFMAs round at the block's magnitude; the blocks then add up in fp32. One running
+// accumulator over all of K instead rounds three times per 16 inputs: relative error 5.5e-7 at K = 2560
+// and 1.1e-6 at 9728, against 1.3e-7 and 2.3e-7 for the 64-lane fp32 GEMV and 1.3e-7 and 2.3e-7 (less
+// with K splits) this way, at the same speed.
+//
+// Bound: MFMA and LDS bandwidth (three planes of A against one of W: 128 x 128 tiles read 85 and write
+// 42 of the 128 LDS bytes per clock at full MFMA rate). 1501 rows of the 4B-class projections run at
+// 300 TFLOP/s (900 of MFMA), where a large bf16 library product reaches 1375 on the same card; the
+// 8-row GEMVs this replaces gave 8.4.
+//
+// Workgroup b runs on XCD b % 8: each XCD takes a contiguous range of the tiles, rows fastest, so the
+// row tiles that share a weight tile share an L2.
+template <int WM, int WN, int NWM, int NWN, int BK, int KIND>
+__global__ __launch_bounds__(kWG, 2) void k_pf_gemm(GemmArgs G) {
+  constexpr int BM = WM * NWM, BN = WN * NWN, NCH = BK / 8, ROWS = 3 * BM + BN, CPT = ROWS * NCH / kWG;
+  constexpr int BUF = ROWS * BK * 2, TM = WM / 32, TN = WN / 32, NS = BK / 16;
+  static_assert(NWM * NWN == 4 && ROWS * NCH % kWG == 0, "four waves, whole loads");
+  static_assert(BK == 32 || BK == 64, "a block of 64 inputs is one or two steps");
+  extern __shared__ __align__(16) char plds[];
+  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
+  int b = blockIdx.x;
+  {
+    const int T = gridDim.x, per = T / 8, rem = T % 8, xcd = b % 8, j = b / 8;
+    b = xcd * per + min(xcd, rem) + j;
+  }
+  const int mi = b % G.mt, ni = (b / G.mt) % G.nt, z = b / (G.mt * G.nt);
+  const int m0 = mi * BM, n0 = ni * BN;
+  const int kb = z * G.KS, ke = min(G.K, kb + G.KS);
+  const int half = G.out.dh >> 1;
+
+  // source of this thread's chunk i: row R = plane * BM + row, or a weight row (rows past the matrix
+  // re-read its last one; their results are not stored)
+  const uint16_t* src[CPT];
+  int kc[CPT];
+#pragma unroll
+  for (int i = 0; i < CPT; i++) {
+    const int t = i * kWG + tid, row = t / NCH, c = (t % NCH) ^ (NCH == 4 ? (row >> 1) & 3 : row & 7);
+    kc[i] = c * 8;
+    if (row < 3 * BM) {
+      src[i] = G.a.p + (row / BM) * G.a.stride + (size_t)min(m0 + row % BM, G.M - 1) * G.K + c * 8;
+    } else {
+      const int rb = row - 3 * BM;
+      const uint16_t* W = G.w0;
+      size_t n;
+      if (KIND == GK_PLAIN) {
+        n = min(n0 + rb, G.cols - 1);
+      } else {
+        const int which = (rb >> 5) & 1, q = min((n0 >> 1) + (rb >> 6) * 32 + (rb & 31), G.cols - 1);
+        if (KIND == GK_GATEUP) {
+          n = q;
+          if (which) W = G.w1;
+        } else {
+          const int head = q / half, j = q - head * half;
+          int hr = head;
+          if (head >= G.out.hq) {
+            hr -= G.out.hq;
+            W = G.w1;
+            if (hr >= G.out.hkv) {
+              hr -= G.out.hkv;
+              W = G.w2;
+            }
+          }
+          n = (size_t)hr * G.out.dh + j + which * half;
+        }
+      }
+      src[i] = W + n * G.ldw + c * 8;
+    }
+  }
+  auto issue = [&](int buf, int k) {  // inputs k .. k + BK (zeros past the split's end)
+#pragma unroll
+    for (int i = 0; i < CPT; i++) {
+      const uint16_t* p = k + kc[i] < ke ? src[i] + k : G.zeros;
+      __builtin_amdgcn_global_load_lds((gbytes*)p, (lbytes*)(plds + buf * BUF + (i * kWG + w * 64) * 16), 16, 0, 0);
+    }
+  };
+  // every wave's loads have landed, and every wave is done with the buffer that is loaded next
+  auto arrive = [&]() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+
+  const int wm = w % NWM, wn = w / NWM, r = lane & 31, h = lane >> 5;
+  const int sw = NCH == 4 ? (r >> 1) & 3 : r & 7;
+  auto frag = [&](const char* base, int row, int s) {  // MFMA operand of inputs 16 s ..: lane row r, half h
+    return *reinterpret_cast<const bf16x8*>(base + (row + r) * BK * 2 + (((2 * s + h) ^ sw) << 4));
+  };
+  f32x16 tot[TM][TN], acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; i++)
+#pragma unroll
+    for (int j = 0; j < TN; j++) tot[i][j] = (f32x16)(0.f);
+  auto mul = [&](const bf16x8 (&a)[TM], const bf16x8 (&bw)[TN], bool first) {
+#pragma unroll
+    for (int i = 0; i < TM; i++)
+#pragma unroll
+      for (int j = 0; j < TN; j++)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], bw[j], first ? (f32x16)(0.f) : acc[i][j], 0, 0, 0);
+  };
+  auto load_w = [&](const char* base, bf16x8 (&bw)[NS][TN]) {
+#pragma unroll
+    for (int s = 0; s < NS; s++)
+#pragma unroll
+      for (int j = 0; j < TN; j++) bw[s][j] = frag(base, 3 * BM + wn * WN + j * 32, s);
+  };
+  auto load_a = [&](const char* base, int p, int s, bf16x8 (&a)[TM]) {
+#pragma unroll
+    for (int i = 0; i < TM; i++) a[i] = frag(base, p * BM + wm * WM + i * 32, s);
+  };
+  auto planes = [&](const char* base, int p_last, const bf16x8 (&bw)[NS][TN], bool fresh) {  // lo, mid(, hi)
+#pragma unroll
+    for (int p = 2; p >= p_last; p--)
+#pragma unroll
+      for (int s = 0; s < NS; s++) {
+        bf16x8 a[TM];
+        load_a(base, p, s, a);
+        mul(a, bw[s], fresh && p == 2 && s == 0);
+      }
+  };
+  auto fold = [&]() {
+#pragma unroll
+    for (int i = 0; i < TM; i++)
+#pragma unroll
+      for (int j = 0; j < TN; j++)
+#pragma unroll
+        for (int v = 0; v < 16; v++) tot[i][j][v] += acc[i][j][v];
+  };
+
+  issue(0, kb);
+  if constexpr (BK == 64) {
+    int buf = 0;
+    for (int k = kb; k < ke; k += BK, buf ^= 1) {
+      arrive();
+      if (k + BK < ke) issue(buf ^ 1, k + BK);
+      bf16x8 bw[NS][TN];
+      load_w(plds + buf * BUF, bw);
+      planes(plds + buf * BUF, 0, bw, true);
+      fold();
+    }
+  } else {
+    for (int k = kb; k < ke; k += 2 * BK) {
+      bf16x8 w0[NS][TN], w1[NS][TN], hi0[NS][TM];
+      arrive();
+      if (k + BK < ke) issue(1, k + BK);
+      load_w(plds, w0);
+#pragma unroll
+      for (int s = 0; s < NS; s++) load_a(plds, 0, s, hi0[s]);  // hi waits for the block's small products
+      planes(plds, 1, w0, true);
+      const bool second = k + BK < ke;
+      if (second) {
+        arrive();
+        if (k + 2 * BK < ke) issue(0, k + 2 * BK);
+        load_w(plds + BUF, w1);
+        planes(plds + BUF, 1, w1, false);
+      }
+#pragma unroll
+      for (int s = 0; s < NS; s++) mul(hi0[s], w0[s], false);
+      if (second) {
+#pragma unroll
+        for (int s = 0; s < NS; s++) {
+          bf16x8 a[TM];
+          load_a(plds + BUF, 0, s, a);
+          mul(a, w1[s], false);
+        }
+      }
+      fold();
+    }
+  }
+
+  // register v of lane l: row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32
+  const int mr = m0 + wm * WM + 4 * h;
+  if (KIND == GK_PLAIN || G.part != nullptr) {
+    const int ncol = KIND == GK_PLAIN ? G.cols : 2 * G.cols;
+    float* o = G.part + (size_t)z * G.M * ncol;
+#pragma unroll
+    for (int j = 0; j < TN; j++) {
+      const int cb = wn * WN + j * 32;  // column block of the tile
+      int col;
+      bool ok;
+      if (KIND == GK_PLAIN) {
+        col = n0 + cb + r;
+        ok = col < G.cols;
+      } else {  // both columns of pair q at q and cols + q
+        const int q = (n0 >> 1) + (cb >> 6) * 32 + r;
+        col = ((cb >> 5) & 1) * G.cols + q;
+        ok = q < G.cols;
+      }
+#pragma unroll
+      for (int i = 0; i < TM; i++)
+#pragma unroll
+        for (int v = 0; v < 16; v++) {
+          const int m = mr + i * 32 + 8 * (v >> 2) + (v & 3);
+          if (ok && m < G.M) o[(size_t)m * ncol + col] = tot[i][j][v];
+        }
+    }
+  } else if constexpr (KIND != GK_PLAIN && TN % 2 == 0) {
+#pragma unroll
+    for (int jp = 0; jp < TN / 2; jp++) {
+      const int q = ((n0 + wn * WN) >> 1) + jp * 32 + r;
+#pragma unroll
+      for (int i = 0; i < TM; i++)
+#pragma unroll
+        for (int v = 0; v < 16; v++) {
+          const int m = mr + i * 32 + 8 * (v >> 2) + (v & 3);
+          if (q >= G.cols || m >= G.M) continue;
+          const float sc = G.out.rs[m], s0 = tot[i][2 * jp][v] * sc, s1 = tot[i][2 * jp + 1][v] * sc;
+          if (KIND == GK_QKV)
+            qkv_store(G.out, m, q, s0, s1);
+          else
+            act_store(G.out, m, q, s0, s1);
+        }
+    }
+  }
+}
+
+// The pair epilogue of a K-split projection: the splits added in order. Grid: x pairs, y rows.
+template <int KIND>
+__global__ __launch_bounds__(kWG) void k_pf_pairs(PairOut O, const float* part, int S, int M, int pairs) {
+  const int q = blockIdx.x * kWG + threadIdx.x, m = blockIdx.y;
+  if (q >= pairs) return;
+  float s0 = 0.f, s1 = 0.f;
+  for (int s = 0; s < S; s++) {
+    const float* p = part + ((size_t)s * M + m) * 2 * pairs + q;
+    s0 += p[0];
+    s1 += p[pairs];
+  }
+  const float sc = O.rs[m];
+  if (KIND == GK_QKV)
+    qkv_store(O, m, q, s0 * sc, s1 * sc);
+  else
+    act_store(O, m, q, s0 * sc, s1 * sc);
+}
+
+// --------------------------------------------------------------------------------- causal attention
+// Rows at positions pos0 .. pos0 + M - 1 over one layer's paged bf16 cache, which already holds their
+// keys. A workgroup serves 128 queries (128 / G rows x the G heads of KV head g), 32 per wave, and
+// walks the keys in tiles of 64 up to its last row's position:
+//   * S^T = K Q^T (lane l: query l % 32, 16 keys per 32-key block), q in registers as three planes;
+//   * the softmax of a query is a max and a sum over the lane's keys and one exchange with lane l ^ 32
+//     (base 2: the queries are scaled by log2(e) / sqrt(dh));
+//   * O^T += V^T P^T with p cut into planes in registers: the eight keys that half h of k step s needs
+//     are the ones the lane already holds, if V^T keeps its key quads in the order 0, 2, 1, 3.
+// K goes to LDS with direct loads, V through registers, where 4 x 8 blocks are transposed.
+// Bound: MFMA (48 per 32 keys) beside the softmax's vector work.
+struct AttnArgs {
+  const float* q;
+  Planes out;                 // [M][Hq*dh]
+  const uint16_t* kv;
+  const int32_t* page_table;
+  int M, pos0, G, hkv, max_pages;
+  float qscale;
+};
+
+template <int DH>
+__global__ __launch_bounds__(kWG, 2) void k_pf_attn(AttnArgs A) {
+  constexpr int KT = 64, NT = DH / 32, KS = DH / 16, NCH = DH / 8, PAGE = 16;
+  constexpr int KBUF = KT * DH * 2, VBUF = DH * KT * 2, BUF = KBUF + VBUF;
+  constexpr int KPT = KT * NCH / kWG;          // K chunks per thread (one page each pass)
+  constexpr int VTH = KT / 4 * (DH / 8);       // threads with a 4 x 8 block of V
+  extern __shared__ __align__(16) char plds[];
+  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, col = lane & 31, h = lane >> 5;
+  const int g = blockIdx.x, G = A.G, rpw = 128 / G;
+  const int row0 = ((int)gridDim.y - 1 - (int)blockIdx.y) * rpw;  // the longest rows first
+  const int qd = A.hkv * G * DH;
+  const int qi = w * 32 + col, qr = min(row0 + qi / G, A.M - 1), qh = g * G + qi % G;
+  const int qlim = A.pos0 + qr;                                   // last key of this lane's query
+  const int kend = A.pos0 + min(row0 + rpw, A.M);                 // keys of the workgroup: [0, kend)
+  const int tiles = (kend + KT - 1) / KT;
+  const size_t page_elems = (size_t)2 * A.hkv * PAGE * DH, head_off = (size_t)g * PAGE * DH;
+  const size_t voff = (size_t)A.hkv * PAGE * DH;
+
+  bf16x8 qf[3][KS];
+  {
+    const float* qp = A.q + (size_t)qr * qd + (size_t)qh * DH + h * 8;
+#pragma unroll
+    for (int s = 0; s < KS; s++) {
+      union { uint16_t u[8]; bf16x8 f; } t[3];
+#pragma unroll
+      for (int e = 0; e < 8; e += 4) {
+        const float4 v = *reinterpret_cast<const float4*>(qp + s * 16 + e);
+        const float f[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+          uint32_t a, b, c;
+          split3(f[k] * A.qscale, a, b, c);
+          t[0].u[e + k] = (uint16_t)a;
+          t[1].u[e + k] = (uint16_t)b;
+          t[2].u[e + k] = (uint16_t)c;
+        }
+      }
+#pragma unroll
+      for (int p = 0; p < 3; p++) qf[p][s] = t[p].f;
+    }
+  }
+
+  auto page_at = [&](int i) { return A.page_table[min(i, A.max_pages - 1)]; };
+  auto issue_k = [&](int buf, int t) {
+#pragma unroll
+    for (int i = 0; i < KPT; i++) {
+      const int ch = i * kWG + tid, key = ch / NCH, c = (ch % NCH) ^ (key & 7);
+      const uint16_t* p = A.kv + (size_t)page_at(t * (KT / PAGE) + key / PAGE) * page_elems + head_off +
+                          (size_t)(key % PAGE) * DH + c * 8;
+      __builtin_amdgcn_global_load_lds((gbytes*)p, (lbytes*)(plds + buf * BUF + (i * kWG + w * 64) * 16), 16, 0, 0);
+    }
+  };
+  // V block of this thread: keys 4 kq .. + 3, dims 8 dg .. + 7
+  const int kq = tid / (DH / 8), dg = tid % (DH / 8);
+  uint4 vr[4];
+  auto load_v = [&](int t) {
+    if (tid >= VTH) return;
+    const uint16_t* p = A.kv + (size_t)page_at(t * (KT / PAGE) + kq / 4) * page_elems + head_off + voff +
+                        (size_t)((kq & 3) * 4) * DH + dg * 8;
+#pragma unroll
+    for (int j = 0; j < 4; j++) vr[j] = *reinterpret_cast<const uint4*>(p + j * DH);
+  };
+  auto store_v = [&](int buf, int t) {
+    if (tid >= VTH) return;
+    const int key = t * KT + kq * 4;  // keys past the end may hold anything: zeros, so that 0 * v is 0
+#pragma unroll
+    for (int j = 0; j < 4; j++)
+      if (key + j >= kend) vr[j] = make_uint4(0u, 0u, 0u, 0u);
+    const int slot = (kq & ~3) + ((kq & 1) << 1) + ((kq >> 1) & 1);
+    char* vt = plds + buf * BUF + KBUF;
+    const uint32_t* a = reinterpret_cast<const uint32_t*>(&vr[0]);
+#pragma unroll
+    for (int e = 0; e < 8; e++) {
+      const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;
+      const uint32_t x = __builtin_amdgcn_perm(a[4 + (e >> 1)], a[e >> 1], sel);
+      const uint32_t y = __builtin_amdgcn_perm(a[12 + (e >> 1)], a[8 + (e >> 1)], sel);
+      const int dim = dg * 8 + e, ch = (slot >> 1) ^ ((dim ^ (dim >> 3)) & 7);
+      *reinterpret_cast<uint2*>(vt + dim * (KT * 2) + ch * 16 + (slot & 1) * 8) = make_uint2(x, y);
+    }
+  };
+
+  f32x16 o[NT];
+#pragma unroll
+  for (int t = 0; t < NT; t++) o[t] = (f32x16)(0.f);
+  float m_run = -INFINITY, l_run = 0.f;
+
+  issue_k(0, 0);
+  load_v(0);
+  store_v(0, 0);
+  for (int t = 0; t < tiles; t++) {
+    const int buf = t & 1;
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    const bool more = t + 1 < tiles;
+    if (more) {
+      issue_k(buf ^ 1, t + 1);
+      load_v(t + 1);
+    }
+    const char* kt = plds + buf * BUF;
+    const char* vt = kt + KBUF;
+    f32x16 s[2];
+#pragma unroll
+    for (int b = 0; b < 2; b++) {
+      const int key = b * 32 + col;
+      const int sw = key & 7;
+#pragma unroll
+      for (int k = 0; k < KS; k++) {
+        const bf16x8 kf = *reinterpret_cast<const bf16x8*>(kt + key * DH * 2 + (((2 * k + h) ^ sw) << 4));
+#pragma unroll
+        for (int p = 2; p >= 0; p--)
+          s[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[p][k], (p == 2 && k == 0) ? (f32x16)(0.f) : s[b], 0, 0, 0);
+      }
+    }
+    if ((t + 1) * KT > A.pos0 + row0) {  // keys past some row of the workgroup
+#pragma unroll
+      for (int b = 0; b < 2; b++)
+#pragma unroll
+        for (int v = 0; v < 16; v++) {
+          const int key = t * KT + b * 32 + 8 * (v >> 2) + 4 * h + (v & 3);
+          if (key > qlim) s[b][v] = -INFINITY;
+        }
+    }
+    float mx = -INFINITY;
+#pragma unroll
+    for (int b = 0; b < 2; b++)
+#pragma unroll
+      for (int v = 0; v < 16; v++) mx = fmaxf(mx, s[b][v]);
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    const float mn = fmaxf(m_run, mx);  // finite: key 0 is every row's
+    if (__any(mn > m_run)) {
+      const float al = exp2f(m_run - mn);
+      l_run *= al;
+#pragma unroll
+      for (int tt = 0; tt < NT; tt++)
+#pragma unroll
+        for (int v = 0; v < 16; v++) o[tt][v] *= al;
+      m_run = mn;
+    }
+    float ps = 0.f;
+#pragma unroll
+    for (int b = 0; b < 2; b++)
+#pragma unroll
+      for (int k = 0; k < 2; k++) {
+        union { uint32_t u[4]; bf16x8 f; } pf[3];
+#pragma unroll
+        for (int e = 0; e < 8; e += 2) {
+          const float p0 = exp2f(s[b][8 * k + e] - m_run), p1 = exp2f(s[b][8 * k + e + 1] - m_run);
+          ps += p0 + p1;
+          // truncated planes of a finite p >= 0
+          const uint32_t h0 = __float_as_uint(p0), h1 = __float_as_uint(p1);
+          const float r0 = p0 - __uint_as_float(h0 & 0xffff0000u), r1 = p1 - __uint_as_float(h1 & 0xffff0000u);
+          const uint32_t m0 = __float_as_uint(r0), m1 = __float_as_uint(r1);
+          const uint32_t l0 = __float_as_uint(r0 - __uint_as_float(m0 & 0xffff0000u));
+          const uint32_t l1 = __float_as_uint(r1 - __uint_as_float(m1 & 0xffff0000u));
+          pf[0].u[e >> 1] = __builtin_amdgcn_perm(h1, h0, 0x07060302u);
+          pf[1].u[e >> 1] = __builtin_amdgcn_perm(m1, m0, 0x07060302u);
+          pf[2].u[e >> 1] = __builtin_amdgcn_perm(l1, l0, 0x07060302u);
+        }
+        const int c = 2 * (2 * b + k) + h;  // 16-byte chunk of V^T's row: this half's eight keys
+#pragma unroll
+        for (int tt = 0; tt < NT; tt++) {
+          const int dim = tt * 32 + col;
+          const bf16x8 vf = *reinterpret_cast<const bf16x8*>(vt + dim * (KT * 2) + ((c ^ ((dim ^ (dim >> 3)) & 7)) << 4));
+#pragma unroll
+          for (int p = 2; p >= 0; p--) o[tt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[p].f, o[tt], 0, 0, 0);
+        }
+      }
+    l_run += ps + __shfl_xor(ps, 32, 64);
+    if (more) store_v(buf ^ 1, t + 1);
+  }
+  if (row0 + qi / G >= A.M) return;
+  const float inv = 1.0f / l_run;
+  const size_t at = (size_t)qr * qd + (size_t)qh * DH + 4 * h;
+#pragma unroll
+  for (int tt = 0; tt < NT; tt++)
+#pragma unroll
+    for (int v = 0; v < 16; v += 4)
+      store_planes4(A.out, at + tt * 32 + 2 * v, o[tt][v] * inv, o[tt][v + 1] * inv, o[tt][v + 2] * inv,
+                    o[tt][v + 3] * inv);
+}
+
+// ---------------------------------------------------------------------------------------- launches
+// Row tile and K splits of a projection. Tiles are 128 columns wide and 128 rows high (64 up to 192
+// rows, 32 up to 32: fewer padding rows where the weights' stream is the bound). Two workgroups fit a
+// CU, so 512 run at once; a split costs about 288 inputs' worth of prologue and epilogue.
+struct GemmPlan {
+  int bm, S, KS;
+};
+
+GemmPlan plan_gemm(int M, int cols, int K, size_t part_cap) {
+  GemmPlan p;
+  p.bm = M <= 32 ? 32 : M <= 192 ? 64 : 128;
+  const long long tiles = (long long)((M + p.bm - 1) / p.bm) * ((cols + 127) / 128);
+  long long best = -1;
+  p.S = 1;
+  for (int S = 1; S <= kPrefillMaxSplit; S++) {
+    const int KS = ((K + S - 1) / S + 63) / 64 * 64;
+    if (S > 1 && ((size_t)S * M * cols > part_cap || KS < 256 || (S - 1) * KS >= K)) continue;
+    const long long rounds = (tiles * S + 511) / 512, cost = rounds * (KS + 288);
+    if (best < 0 || cost < best) {
+      best = cost;
+      p.S = S;
+    }
+  }
+  p.KS = ((K + p.S - 1) / p.S + 63) / 64 * 64;
+  return p;
+}
+
+template <int WM, int WN, int NWM, int NWN, int BK, int KIND>
+void launch_gemm(GemmArgs G, int S, hipStream_t s) {
+  constexpr int BM = WM * NWM, BN = WN * NWN;
+  const int ncol = KIND == GK_PLAIN ? G.cols : 2 * G.cols;
+  G.mt = (G.M + BM - 1) / BM;
+  G.nt = (ncol + BN - 1) / BN;
+  const size_t shm = (size_t)2 * (3 * BM + BN) * BK * 2;
+  launch_timed((k_pf_gemm<WM, WN, NWM, NWN, BK, KIND>), dim3(G.mt * G.nt * S), dim3(kWG), shm, s, G);
+}
+
+// One projection; returns the number of partial sums left in B.part (0: the pair epilogue has run).
+template <int KIND>
+int gemm(const PrefillBufs& B, GemmArgs G, hipStream_t s) {
+  const int ncol = KIND == GK_PLAIN ? G.cols : 2 * G.cols;
+  const GemmPlan p = plan_gemm(G.M, ncol, G.K, B.part_cap);
+  G.KS = p.KS;
+  G.zeros = B.zeros;
+  // pairs meet in one lane only in the two-tile waves of the taller shapes
+  const bool direct = KIND != GK_PLAIN && p.S == 1 && p.bm > 32;
+  G.part = direct ? nullptr : B.part;
+  if (p.bm == 32)
+    launch_gemm<32, 32, 1, 4, 64, KIND>(G, p.S, s);
+  else if (p.bm == 64)
+    launch_gemm<32, 64, 2, 2, 64, KIND>(G, p.S, s);
+  else
+    launch_gemm<64, 64, 2, 2, 32, KIND>(G, p.S, s);
+  if constexpr (KIND == GK_PLAIN) {
+    return p.S;
+  } else {
+    if (!direct)
+      launch_timed((k_pf_pairs<KIND>), dim3((G.cols + kWG - 1) / kWG, G.M), dim3(kWG), 0, s, G.out,
+                   (const float*)B.part, p.S, G.M, G.cols);
+    return 0;
+  }
+}
+
+void attention(const Ctx& C, AttnArgs A, hipStream_t s) {
+  const int rpw = 128 / A.G;
+  const dim3 grid(A.hkv, (A.M + rpw - 1) / rpw);
+  const size_t shm = (size_t)2 * 2 * 64 * C.dh * 2;
+  if (C.dh == 128)
+    launch_timed((k_pf_attn<128>), grid, dim3(kWG), shm, s, A);
+  else
+    launch_timed((k_pf_attn<64>), grid, dim3(kWG), shm, s, A);
+}
+
+}  // namespace
+
+int prefill_rows(int max_tokens) { return std::min(kPrefillRows, (max_tokens + 127) / 128 * 128); }
+
+// Partial sums: four splits of the narrow projections over a full chunk, and of the wide ones over a
+// chunk of 128 rows (longer chunks have tiles enough without splitting those).
+size_t prefill_part_floats(int rows, int d, int F, int qkv_cols) {
+  return std::max((size_t)4 * rows * d, (size_t)4 * 128 * std::max(2 * F, qkv_cols));
+}
+
+void prefill_mfma(const Ctx& C, const PrefillBufs& B, const LayerDesc* layers, int len, void* stream, int* last_row) {
+  hipStream_t s = (hipStream_t)stream;
+  const int d = C.d, qkv_pairs = (C.hq + 2 * C.hkv) * (C.dh / 2);
+  const int nch = (len + kPrefillRows - 1) / kPrefillRows;
+  const int step = ((len + nch - 1) / nch + 127) / 128 * 128;  // equal chunks
+  const size_t pa_w = std::max(d, C.qdim), pb_w = std::max(d, C.F);
+  const Planes pa{B.pa, (size_t)B.rows * pa_w}, pb{B.pb, (size_t)B.rows * pb_w};
+
+  for (int t0 = 0; t0 < len; t0 += step) {
+    const int M = std::min(step, len - t0);
+    const bool last = t0 + M == len;
+    int S = 0;  // partial sums that wait in B.part
+    auto norm = [&](float* x, int rows, int base, const float* gain, bool raw) {
+      NormArgs N{};
+      N.x = x;
+      N.d = d;
+      N.S = S;
+      N.base = base;
+      N.part = B.part;
+      N.part_stride = (size_t)rows * d;
+      N.tok = C.tok + t0;
+      N.embed = (const uint16_t*)C.embed;
+      N.gain = gain;
+      N.eps = C.eps;
+      N.out = pa;
+      if (raw) N.raw = pb;
+      N.rs = B.rs;
+      launch_timed(k_pf_norm, dim3(rows), dim3(kWG), 0, s, N);
+      S = 0;
+    };
+    auto plain = [&](const Planes& a, int rows, int K, const void* w, int ldw) {
+      GemmArgs G{};
+      G.a = a;
+      G.w0 = (const uint16_t*)w;
+      G.M = rows;
+      G.K = K;
+      G.ldw = ldw;
+      G.cols = d;
+      S = gemm<GK_PLAIN>(B, G, s);
+    };
+    auto qkv = [&](const LayerDesc& L) {
+      GemmArgs G{};
+      G.a = pa;
+      G.w0 = (const uint16_t*)L.wq;
+      G.w1 = (const uint16_t*)L.wk;
+      G.w2 = (const uint16_t*)L.wv;
+      G.M = M;
+      G.K = d;
+      G.ldw = d;
+      G.cols = qkv_pairs;
+      G.out.rs = B.rs;
+      G.out.q = B.q;
+      G.out.kv = (uint16_t*)L.kv;
+      G.out.page_table = C.page_table;
+      G.out.rope = C.rope;
+      G.out.pos0 = t0;
+      G.out.hq = C.hq;
+      G.out.hkv = C.hkv;
+      G.out.dh = C.dh;
+      G.out.page = C.page;
+      gemm<GK_QKV>(B, G, s);
+    };
+    // attention, O-proj, MLP of rows r0 .. M - 1; leaves the down projection's partial sums
+    auto rest = [&](const LayerDesc& L, float* x, int r0) {
+      const int rows = M - r0;
+      AttnArgs A{};
+      A.q = B.q + (size_t)r0 * C.qdim;
+      A.out = pa;
+      A.kv = (const uint16_t*)L.kv;
+      A.page_table = C.page_table;
+      A.M = rows;
+      A.pos0 = t0 + r0;
+      A.G = C.G;
+      A.hkv = C.hkv;
+      A.max_pages = C.max_pages;
+      A.qscale = C.scale * 1.44269504088896340736f;
+      attention(C, A, s);
+      plain(pa, rows, C.qdim, L.wo, C.qdim);
+      norm(x + (size_t)r0 * d, rows, 0, L.mlp_norm, false);
+      GemmArgs G{};
+      G.a = pa;
+      G.w0 = (const uint16_t*)L.wg;
+      G.w1 = (const uint16_t*)L.wu;
+      G.M = rows;
+      G.K = d;
+      G.ldw = d;
+      G.cols = C.F;
+      G.out.rs = B.rs;
+      G.out.act = pb;
+      G.out.F = C.F;
+      gemm<GK_GATEUP>(B, G, s);
+      plain(pb, rows, C.F, L.wd, C.F);
+    };
+
+    int stage = 0;
+    for (int l = 0; l < C.L; l++) {
+      const bool opens = stage < C.n && l == C.beta[stage];  // a stage's input is an anchor
+      norm(B.x, M, l == 0 ? 1 : 0, layers[l].attn_norm, opens);
+      if (opens) {  // the draft module's feature projection, one anchor's columns at a time
+        plain(pb, M, d, (const uint16_t*)C.w_in + (size_t)stage * d, C.n * d);
+        norm(B.px, M, stage == 0 ? 2 : 0, nullptr, false);
+        stage++;
+      }
+      qkv(layers[l]);
+      if (l + 1 < C.L)
+        rest(layers[l], B.x, 0);
+      else if (last) {  // only the prompt's last row is read past the last layer's keys and values
+        rest(layers[l], B.x, M - 1);
+        norm(B.x + (size_t)(M - 1) * d, 1, 0, nullptr, false);
+        *last_row = M - 1;
+      }
+    }
+    for (int i = 0; i < C.ls; i++) {
+      const LayerDesc& L = layers[C.L + i];
+      norm(B.px, M, 0, L.attn_norm, false);
+      qkv(L);
+      if (i + 1 < C.ls) rest(L, B.px, 0);  // the last layer's rows are not read: its caches only
+    }
+  }
+}
+
+}  // namespace spd
