@@ -172,7 +172,7 @@ struct GemmArgs {
   PairOut out;
 };
 
-// C = A W^T over a BM x BN tile: workgroup of four waves, each WM x WN in 32 x 32 MFMA tiles.
+// C = A W^T over a BM x BN tile: a workgroup of NWM x NWN waves, each WM x WN in 32 x 32 MFMA tiles.
 // The three A planes and the W rows of a K step of BK go to LDS with direct 16-byte global loads
 // (double buffered; the 16-byte chunks of a row are permuted so that eight consecutive rows read eight
 // different bank groups). Pair kinds interleave the weights' rows by 32 so that a lane holds both
@@ -184,18 +184,20 @@ struct GemmArgs {
 // and 1.1e-6 at 9728, against 1.3e-7 and 2.3e-7 for the 64-lane fp32 GEMV and 1.3e-7 and 2.3e-7 (less
 // with K splits) this way, at the same speed.
 //
-// Bound: MFMA and LDS bandwidth (three planes of A against one of W: 128 x 128 tiles read 85 and write
-// 42 of the 128 LDS bytes per clock at full MFMA rate). 1501 rows of the 4B-class projections run at
-// 300 TFLOP/s (900 of MFMA), where a large bf16 library product reaches 1375 on the same card; the
-// 8-row GEMVs this replaces gave 8.4.
+// Bound: MFMA issue beside LDS reads (three planes of A against one of W). A workgroup of eight waves
+// over 128 x 256 shares each A tile between four waves: the 4B-class projections of 1501 rows take
+// 434 us (gate/up, 345 TFLOP/s, 1034 of MFMA), 87 (O-proj) and 209 (down), against 510, 103 and 236 for
+// four waves over 128 x 128 twice per CU; a large bf16 library product reaches 1375 TFLOP/s on the same
+// card. Three and four buffers were slower than two (457 to 479 us for gate/up).
 //
 // Workgroup b runs on XCD b % 8: each XCD takes a contiguous range of the tiles, rows fastest, so the
 // row tiles that share a weight tile share an L2.
 template <int WM, int WN, int NWM, int NWN, int BK, int KIND>
-__global__ __launch_bounds__(kWG, 2) void k_pf_gemm(GemmArgs G) {
-  constexpr int BM = WM * NWM, BN = WN * NWN, NCH = BK / 8, ROWS = 3 * BM + BN, CPT = ROWS * NCH / kWG;
+__global__ __launch_bounds__(64 * NWM * NWN, 2) void k_pf_gemm(GemmArgs G) {
+  constexpr int NTH = 64 * NWM * NWN;
+  constexpr int BM = WM * NWM, BN = WN * NWN, NCH = BK / 8, ROWS = 3 * BM + BN, CPT = ROWS * NCH / NTH;
   constexpr int BUF = ROWS * BK * 2, TM = WM / 32, TN = WN / 32, NS = BK / 16;
-  static_assert(NWM * NWN == 4 && ROWS * NCH % kWG == 0, "four waves, whole loads");
+  static_assert(ROWS * NCH % NTH == 0, "whole loads");
   static_assert(BK == 32 || BK == 64, "a block of 64 inputs is one or two steps");
   extern __shared__ __align__(16) char plds[];
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
@@ -215,7 +217,7 @@ __global__ __launch_bounds__(kWG, 2) void k_pf_gemm(GemmArgs G) {
   int kc[CPT];
 #pragma unroll
   for (int i = 0; i < CPT; i++) {
-    const int t = i * kWG + tid, row = t / NCH, c = (t % NCH) ^ (NCH == 4 ? (row >> 1) & 3 : row & 7);
+    const int t = i * NTH + tid, row = t / NCH, c = (t % NCH) ^ (NCH == 4 ? (row >> 1) & 3 : row & 7);
     kc[i] = c * 8;
     if (row < 3 * BM) {
       src[i] = G.a.p + (row / BM) * G.a.stride + (size_t)min(m0 + row % BM, G.M - 1) * G.K + c * 8;
@@ -251,7 +253,7 @@ __global__ __launch_bounds__(kWG, 2) void k_pf_gemm(GemmArgs G) {
 #pragma unroll
     for (int i = 0; i < CPT; i++) {
       const uint16_t* p = k + kc[i] < ke ? src[i] + k : G.zeros;
-      __builtin_amdgcn_global_load_lds((gbytes*)p, (lbytes*)(plds + buf * BUF + (i * kWG + w * 64) * 16), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds((gbytes*)p, (lbytes*)(plds + buf * BUF + (i * NTH + w * 64) * 16), 16, 0, 0);
     }
   };
   // every wave's loads have landed, and every wave is done with the buffer that is loaded next
@@ -418,7 +420,9 @@ __global__ __launch_bounds__(kWG) void k_pf_pairs(PairOut O, const float* part, 
 //   * O^T += V^T P^T with p cut into planes in registers: the eight keys that half h of k step s needs
 //     are the ones the lane already holds, if V^T keeps its key quads in the order 0, 2, 1, 3.
 // K goes to LDS with direct loads, V through registers, where 4 x 8 blocks are transposed.
-// Bound: MFMA (48 per 32 keys) beside the softmax's vector work.
+// Bound: MFMA (48 per 32 keys) beside the softmax's vector work. A layer of the 4B class takes 34 us at
+// 384 rows and 105 us at 1501; the wide model's 2048-row chunks at 6000 tokens 225 us (46, 147 and 343
+// with the page of each tile read where it is used, behind the keys in flight).
 struct AttnArgs {
   const float* q;
   Planes out;                 // [M][Hq*dh]
@@ -470,32 +474,37 @@ __global__ __launch_bounds__(kWG, 2) void k_pf_attn(AttnArgs A) {
     }
   }
 
-  auto page_at = [&](int i) { return A.page_table[min(i, A.max_pages - 1)]; };
-  auto issue_k = [&](int buf, int t) {
+  // The four pages of a key tile, one per lane (mod 4), are read a tile ahead of their use, so that no
+  // wait for a page ever waits for keys or values in flight.
+  auto pages = [&](int t) { return A.page_table[min(t * (KT / PAGE) + (lane & 3), A.max_pages - 1)]; };
+  const int wu = __builtin_amdgcn_readfirstlane(w);
+  auto issue_k = [&](int buf, int pg) {
 #pragma unroll
     for (int i = 0; i < KPT; i++) {
       const int ch = i * kWG + tid, key = ch / NCH, c = (ch % NCH) ^ (key & 7);
-      const uint16_t* p = A.kv + (size_t)page_at(t * (KT / PAGE) + key / PAGE) * page_elems + head_off +
-                          (size_t)(key % PAGE) * DH + c * 8;
+      const int page = __builtin_amdgcn_readlane(pg, (i * kWG + wu * 64) / (NCH * PAGE));
+      const uint16_t* p = A.kv + (size_t)page * page_elems + head_off + (key % PAGE) * DH + c * 8;
       __builtin_amdgcn_global_load_lds((gbytes*)p, (lbytes*)(plds + buf * BUF + (i * kWG + w * 64) * 16), 16, 0, 0);
     }
   };
   // V block of this thread: keys 4 kq .. + 3, dims 8 dg .. + 7
   const int kq = tid / (DH / 8), dg = tid % (DH / 8);
   uint4 vr[4];
-  auto load_v = [&](int t) {
+  auto load_v = [&](int pg) {
     if (tid >= VTH) return;
-    const uint16_t* p = A.kv + (size_t)page_at(t * (KT / PAGE) + kq / 4) * page_elems + head_off + voff +
-                        (size_t)((kq & 3) * 4) * DH + dg * 8;
+    int page = __builtin_amdgcn_readlane(pg, wu * 64 / (DH / 2));
+    if (DH == 64 && lane >= 32) page = __builtin_amdgcn_readlane(pg, wu * 2 + 1);
+    const uint16_t* p = A.kv + (size_t)page * page_elems + head_off + voff + ((kq & 3) * 4) * DH + dg * 8;
 #pragma unroll
     for (int j = 0; j < 4; j++) vr[j] = *reinterpret_cast<const uint4*>(p + j * DH);
   };
   auto store_v = [&](int buf, int t) {
     if (tid >= VTH) return;
-    const int key = t * KT + kq * 4;  // keys past the end may hold anything: zeros, so that 0 * v is 0
+    if ((t + 1) * KT > kend) {  // keys past the end may hold anything: zeros, so that 0 * v is 0
 #pragma unroll
-    for (int j = 0; j < 4; j++)
-      if (key + j >= kend) vr[j] = make_uint4(0u, 0u, 0u, 0u);
+      for (int j = 0; j < 4; j++)
+        if (t * KT + kq * 4 + j >= kend) vr[j] = make_uint4(0u, 0u, 0u, 0u);
+    }
     const int slot = (kq & ~3) + ((kq & 1) << 1) + ((kq >> 1) & 1);
     char* vt = plds + buf * BUF + KBUF;
     const uint32_t* a = reinterpret_cast<const uint32_t*>(&vr[0]);
@@ -514,66 +523,60 @@ __global__ __launch_bounds__(kWG, 2) void k_pf_attn(AttnArgs A) {
   for (int t = 0; t < NT; t++) o[t] = (f32x16)(0.f);
   float m_run = -INFINITY, l_run = 0.f;
 
-  issue_k(0, 0);
-  load_v(0);
+  int pg = pages(0);
+  issue_k(0, pg);
+  load_v(pg);
+  pg = pages(1);
   store_v(0, 0);
   for (int t = 0; t < tiles; t++) {
     const int buf = t & 1;
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
     const bool more = t + 1 < tiles;
     if (more) {
-      issue_k(buf ^ 1, t + 1);
-      load_v(t + 1);
+      issue_k(buf ^ 1, pg);
+      load_v(pg);
+      pg = pages(t + 2);
     }
     const char* kt = plds + buf * BUF;
     const char* vt = kt + KBUF;
-    f32x16 s[2];
 #pragma unroll
-    for (int b = 0; b < 2; b++) {
+    for (int b = 0; b < 2; b++) {  // 32 keys at a time
       const int key = b * 32 + col;
-      const int sw = key & 7;
+      f32x16 s;
 #pragma unroll
       for (int k = 0; k < KS; k++) {
-        const bf16x8 kf = *reinterpret_cast<const bf16x8*>(kt + key * DH * 2 + (((2 * k + h) ^ sw) << 4));
+        const bf16x8 kf = *reinterpret_cast<const bf16x8*>(kt + key * DH * 2 + (((2 * k + h) ^ (col & 7)) << 4));
 #pragma unroll
         for (int p = 2; p >= 0; p--)
-          s[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[p][k], (p == 2 && k == 0) ? (f32x16)(0.f) : s[b], 0, 0, 0);
+          s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[p][k], (p == 2 && k == 0) ? (f32x16)(0.f) : s, 0, 0, 0);
       }
-    }
-    if ((t + 1) * KT > A.pos0 + row0) {  // keys past some row of the workgroup
+      if (t * KT + b * 32 + 31 > A.pos0 + row0) {  // keys past some row of the workgroup
 #pragma unroll
-      for (int b = 0; b < 2; b++)
+        for (int v = 0; v < 16; v++)
+          if (t * KT + b * 32 + 8 * (v >> 2) + 4 * h + (v & 3) > qlim) s[v] = -INFINITY;
+      }
+      float mx = s[0];
 #pragma unroll
-        for (int v = 0; v < 16; v++) {
-          const int key = t * KT + b * 32 + 8 * (v >> 2) + 4 * h + (v & 3);
-          if (key > qlim) s[b][v] = -INFINITY;
-        }
-    }
-    float mx = -INFINITY;
+      for (int v = 1; v < 16; v++) mx = fmaxf(mx, s[v]);
+      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+      const float mn = fmaxf(m_run, mx);  // finite: key 0 is every row's
+      if (__any(mn > m_run)) {
+        const float al = __builtin_amdgcn_exp2f(m_run - mn);
+        l_run *= al;
 #pragma unroll
-    for (int b = 0; b < 2; b++)
+        for (int tt = 0; tt < NT; tt++)
 #pragma unroll
-      for (int v = 0; v < 16; v++) mx = fmaxf(mx, s[b][v]);
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-    const float mn = fmaxf(m_run, mx);  // finite: key 0 is every row's
-    if (__any(mn > m_run)) {
-      const float al = exp2f(m_run - mn);
-      l_run *= al;
-#pragma unroll
-      for (int tt = 0; tt < NT; tt++)
-#pragma unroll
-        for (int v = 0; v < 16; v++) o[tt][v] *= al;
-      m_run = mn;
-    }
-    float ps = 0.f;
-#pragma unroll
-    for (int b = 0; b < 2; b++)
+          for (int v = 0; v < 16; v++) o[tt][v] *= al;
+        m_run = mn;
+      }
+      float ps = 0.f;
 #pragma unroll
       for (int k = 0; k < 2; k++) {
         union { uint32_t u[4]; bf16x8 f; } pf[3];
 #pragma unroll
         for (int e = 0; e < 8; e += 2) {
-          const float p0 = exp2f(s[b][8 * k + e] - m_run), p1 = exp2f(s[b][8 * k + e + 1] - m_run);
+          const float p0 = __builtin_amdgcn_exp2f(s[8 * k + e] - m_run);
+          const float p1 = __builtin_amdgcn_exp2f(s[8 * k + e + 1] - m_run);
           ps += p0 + p1;
           // truncated planes of a finite p >= 0
           const uint32_t h0 = __float_as_uint(p0), h1 = __float_as_uint(p1);
@@ -594,7 +597,8 @@ __global__ __launch_bounds__(kWG, 2) void k_pf_attn(AttnArgs A) {
           for (int p = 2; p >= 0; p--) o[tt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[p].f, o[tt], 0, 0, 0);
         }
       }
-    l_run += ps + __shfl_xor(ps, 32, 64);
+      l_run += ps + __shfl_xor(ps, 32, 64);
+    }
     if (more) store_v(buf ^ 1, t + 1);
   }
   if (row0 + qi / G >= A.M) return;
@@ -609,9 +613,12 @@ __global__ __launch_bounds__(kWG, 2) void k_pf_attn(AttnArgs A) {
 }
 
 // ---------------------------------------------------------------------------------------- launches
-// Row tile and K splits of a projection. Tiles are 128 columns wide and 128 rows high (64 up to 192
-// rows, 32 up to 32: fewer padding rows where the weights' stream is the bound). Two workgroups fit a
-// CU, so 512 run at once; a split costs about 288 inputs' worth of prologue and epilogue.
+// Tile and K splits of a projection. Above 192 rows the tiles are 128 x 256, one eight-wave workgroup
+// per CU; up to 192 rows 64 x 128 and up to 32 rows 32 x 128, two workgroups per CU: fewer padding rows
+// and more workgroups where the weights' stream is the bound (19456 x 2560 at 128 rows: 55 us against
+// 107 us; at 45 rows 39 us). The splits are those of the least cost, in inputs of one tile: a round of
+// workgroups costs its inputs plus about 288 of prologue and epilogue, a split the traffic of its
+// partial sums (QKV at 1501 rows: one split 205 us, two 156 + 22 us of pair epilogue).
 struct GemmPlan {
   int bm, S, KS;
 };
@@ -619,14 +626,15 @@ struct GemmPlan {
 GemmPlan plan_gemm(int M, int cols, int K, size_t part_cap) {
   GemmPlan p;
   p.bm = M <= 32 ? 32 : M <= 192 ? 64 : 128;
-  const long long tiles = (long long)((M + p.bm - 1) / p.bm) * ((cols + 127) / 128);
-  long long best = -1;
+  const int bn = p.bm == 128 ? 256 : 128, slots = p.bm == 128 ? 256 : 512;
+  const long long tiles = (long long)((M + p.bm - 1) / p.bm) * ((cols + bn - 1) / bn);
+  double best = 0.0;
   p.S = 1;
   for (int S = 1; S <= kPrefillMaxSplit; S++) {
     const int KS = ((K + S - 1) / S + 63) / 64 * 64;
     if (S > 1 && ((size_t)S * M * cols > part_cap || KS < 256 || (S - 1) * KS >= K)) continue;
-    const long long rounds = (tiles * S + 511) / 512, cost = rounds * (KS + 288);
-    if (best < 0 || cost < best) {
+    const double cost = (double)((tiles * S + slots - 1) / slots) * (KS + 288) + (S > 1 ? S * 3.3e-5 * M * cols : 0.0);
+    if (S == 1 || cost < best) {
       best = cost;
       p.S = S;
     }
@@ -642,7 +650,7 @@ void launch_gemm(GemmArgs G, int S, hipStream_t s) {
   G.mt = (G.M + BM - 1) / BM;
   G.nt = (ncol + BN - 1) / BN;
   const size_t shm = (size_t)2 * (3 * BM + BN) * BK * 2;
-  launch_timed((k_pf_gemm<WM, WN, NWM, NWN, BK, KIND>), dim3(G.mt * G.nt * S), dim3(kWG), shm, s, G);
+  launch_timed((k_pf_gemm<WM, WN, NWM, NWN, BK, KIND>), dim3(G.mt * G.nt * S), dim3(64 * NWM * NWN), shm, s, G);
 }
 
 // One projection; returns the number of partial sums left in B.part (0: the pair epilogue has run).
@@ -660,7 +668,7 @@ int gemm(const PrefillBufs& B, GemmArgs G, hipStream_t s) {
   else if (p.bm == 64)
     launch_gemm<32, 64, 2, 2, 64, KIND>(G, p.S, s);
   else
-    launch_gemm<64, 64, 2, 2, 32, KIND>(G, p.S, s);
+    launch_gemm<64, 64, 2, 4, 32, KIND>(G, p.S, s);
   if constexpr (KIND == GK_PLAIN) {
     return p.S;
   } else {
@@ -685,10 +693,11 @@ void attention(const Ctx& C, AttnArgs A, hipStream_t s) {
 
 int prefill_rows(int max_tokens) { return std::min(kPrefillRows, (max_tokens + 127) / 128 * 128); }
 
-// Partial sums: four splits of the narrow projections over a full chunk, and of the wide ones over a
-// chunk of 128 rows (longer chunks have tiles enough without splitting those).
+// Partial sums: four splits of the narrow projections and two of QKV over a full chunk, and four of the
+// wide ones over a chunk of 128 rows (longer chunks have tiles enough without splitting those).
 size_t prefill_part_floats(int rows, int d, int F, int qkv_cols) {
-  return std::max((size_t)4 * rows * d, (size_t)4 * 128 * std::max(2 * F, qkv_cols));
+  return std::max(std::max((size_t)4 * rows * d, (size_t)2 * rows * qkv_cols),
+                  (size_t)4 * 128 * std::max(2 * F, qkv_cols));
 }
 
 void prefill_mfma(const Ctx& C, const PrefillBufs& B, const LayerDesc* layers, int len, void* stream, int* last_row) {
