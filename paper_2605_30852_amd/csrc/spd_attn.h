@@ -111,13 +111,16 @@ __device__ __forceinline__ void lds_row(const T* p, float* o) {
 // so each m is finite) in split order into its G output rows. Every thread of the workgroup calls it.
 // All (m, l) pairs are requested first, then the first batch of partial outputs (only the entries
 // that exist: the records are read past the L2, where a repeated address costs as much as a new
-// one), then the (m, l) pairs go to LDS (sm: 2 * kMaxSplits * kAttnMaxQ floats).
-template <int DH>
+// one), then the (m, l) pairs go to LDS (sm: 2 * kMaxSplits * kAttnMaxQ floats). DEV: the records come
+// from workgroups of the same launch (device-scope loads); else from an earlier launch.
+template <int DH, bool DEV = true>
 __device__ __forceinline__ void attn_merge(const float* rec_base, int nsplit, int G, float* out, float* sm) {
   constexpr int MAXQ = kAttnMaxQ, RS = MAXQ * (DH + 2);
   constexpr int NPAIR = MAXQ * DH / 2;
   constexpr int PPT = (NPAIR + kWG - 1) / kWG;
   const int tid = threadIdx.x;
+  auto get = [](const float* p) { return DEV ? ld_dev(p) : *p; };
+  auto get2 = [](const float* p) { return DEV ? ld_dev2(p) : *reinterpret_cast<const float2*>(p); };
   constexpr int MB = kAttnMergeBatch;
   constexpr int MLT = (kMaxSplits * MAXQ + kWG - 1) / kWG;
   float* sl = sm + kMaxSplits * MAXQ;
@@ -127,8 +130,8 @@ __device__ __forceinline__ void attn_merge(const float* rec_base, int nsplit, in
     const int t = tid + i * kWG, sp = t / G, qi = t % G;
     mlm[i] = mll[i] = 0.f;
     if (t < nsplit * G) {
-      mlm[i] = ld_dev(rec_base + (size_t)sp * RS + MAXQ * DH + qi);
-      mll[i] = ld_dev(rec_base + (size_t)sp * RS + MAXQ * DH + MAXQ + qi);
+      mlm[i] = get(rec_base + (size_t)sp * RS + MAXQ * DH + qi);
+      mll[i] = get(rec_base + (size_t)sp * RS + MAXQ * DH + MAXQ + qi);
     }
   }
   const int qi0 = tid / (DH / 2), dp0 = tid % (DH / 2);
@@ -136,7 +139,7 @@ __device__ __forceinline__ void attn_merge(const float* rec_base, int nsplit, in
   float2 ob[MB];
 #pragma unroll
   for (int j = 0; j < MB; j++)
-    ob[j] = (j < nsplit && qi0 < G) ? ld_dev2(rec_base + (size_t)j * RS + qc0 * DH + 2 * dp0) : make_float2(0.f, 0.f);
+    ob[j] = (j < nsplit && qi0 < G) ? get2(rec_base + (size_t)j * RS + qc0 * DH + 2 * dp0) : make_float2(0.f, 0.f);
 #pragma unroll
   for (int i = 0; i < MLT; i++) {
     const int t = tid + i * kWG;
@@ -157,7 +160,7 @@ __device__ __forceinline__ void attn_merge(const float* rec_base, int nsplit, in
         if (i > 0 || sp0 > 0) {
 #pragma unroll
           for (int j = 0; j < MB; j++)
-            ob[j] = ld_dev2(rec_base + (size_t)min(sp0 + j, nsplit - 1) * RS + qi * DH + 2 * dp);
+            ob[j] = get2(rec_base + (size_t)min(sp0 + j, nsplit - 1) * RS + qi * DH + 2 * dp);
         }
 #pragma unroll
         for (int j = 0; j < MB; j++) {
@@ -412,108 +415,123 @@ __device__ bool attn_split_g(const Ctx& C, const KVT* kvb, const float* q, float
   return true;
 }
 
-// ------------------------------------------------------------- row blocks on matrix cores
-// A row block's rows sit at consecutive positions pos0 .. pos0 + nrows - 1 and all read one cache (the
-// draft module's in-flight rows over its KV, Eq. input-seq; a prefill chunk over the prompt), row r's G
-// query heads attending keys 0 .. pos0 + r (causal). One pass over a key split of KV head g then
-// serves all nrows * G <= 32 queries (query j = r * G + h) as the columns of 32x32 fp32 MFMA tiles
-// (v_mfma_f32_32x32x2f32: lane l supplies A[l%32][l/32] and B[l/32][l%32]; accumulator register v of
-// lane l is row 8(v/4) + 4(l/32) + v%4, column l%32). Each wave takes 32-key tiles of the split:
-//   * S^T = K Q^T: k-step kc contracts dims kc and DH/2 + kc, so lane l needs dims (l/32)*DH/2 ..
-//     + DH/2 of key l%32 (one contiguous run, loaded once) and of query l%32 (registers); lane l then
-//     holds query l%32's scores of keys 8(v/4) + 4(l/32) + v%4;
+// ------------------------------------------------------------------ bf16 caches on matrix cores
+// One key split [k0, k0 + chunk) of KV head g for up to 32 / G rows that read the same cache: row r's G
+// query heads attend keys 0 .. lim(r). The nrows * G <= 32 queries (query j = r * G + h) are the columns
+// of 32 x 32 MFMA tiles (v_mfma_f32_32x32x16_bf16: lane l supplies 8 consecutive k of A row l % 32 and
+// of B column l % 32, from k = 8 (l / 32); accumulator register v of lane l is row 8 (v / 4) + 4 (l / 32)
+// + v % 4, column l % 32). The fp32 queries and probabilities are cut into three bf16 planes by
+// truncation (their sum is the fp32 value exactly) and the cache is bf16, so every product is exact and
+// only the order of the sums differs from fp32 FMAs. Each wave takes 32-key tiles of the split:
+//   * S^T = K Q^T: a lane loads its key's dims 16 s + 8 (l / 32) .. + 8 straight into the A operand;
+//     the query planes sit in LDS;
 //   * online softmax per query: a max and a sum over the lane's 16 scores and one exchange with lane
 //     l ^ 32, which holds the query's other 16;
-//   * O^T += V^T P^T: k-step v contracts the two keys of register v, whose probabilities the lanes
-//     already hold as their B operand; A is V^T with row i of dim tile t standing for dim
-//     i * DH/32 + t, so a lane reads the DH/32 values of all tiles as one run of its V row (staged in
-//     a wave-private LDS tile). Lane l ends with query l%32's output over its 16 rows per tile.
-// The products are exact (fp32 operands, fp32 accumulation); against the one-token split only the
-// order of the sums differs. The four waves' (m, l, o) combine in wave order; a row with one split
-// writes its output, otherwise its split record (the one-token split's layout and ticket per row and
-// KV head), and the workgroup that finishes a row's last split merges it in split order.
+//   * O^T += V^T P^T: k step s of half h contracts the eight keys whose probabilities the lane already
+//     holds (registers 8 s .. 8 s + 7); A row i of dim tile t stands for dim i * DH/32 + t, so a lane
+//     reads the DH/32 values of all tiles of a key as one run of its V row (a wave-private LDS tile)
+//     and transposes 8 keys x DH/32 dims in registers.
+// The four waves' (m, l, o) combine in wave order; a row with one split writes its output, otherwise its
+// split record, which attn_merge_row of the launch that follows merges in split order. (With tickets, the
+// workgroup that finished last merged every row of the block one after the other, about 4.6 us each:
+// four rows at 2051 keys took 28.9 us in that form.)
+// Why matrix cores even for one row: a tile costs 48 MFMAs of 32 cycles whatever the number of columns,
+// 0.6 us for 32 keys, where the vector form spends about 2 us of dependent work on 16 keys of a wave;
+// and rows that share a cache read it once. Rows of a launch whose number of queries passes 32 take
+// several workgroups.
 typedef float mfma_acc16 __attribute__((ext_vector_type(16)));
+typedef __bf16 mfma_bf8 __attribute__((ext_vector_type(8)));
 
+// LDS bytes for M queries: query planes and V tiles, reused for the waves' o, then (m, l).
 template <int DH>
-struct RowsMfmaLds {
-  static constexpr int kWaves = kWG / 64;
-  static constexpr size_t kRow = (size_t)DH * 2 + 16;                 // bf16 V row + pad (banks)
-  static constexpr size_t kVTiles = (size_t)kWaves * 32 * kRow;       // per wave [32 keys][DH]
-  static constexpr size_t kO = (size_t)kWaves * 32 * DH * 4;          // per wave o[32 queries][DH]
-  static constexpr size_t kMain = kVTiles > kO ? kVTiles : kO;
-  static constexpr size_t kML = (size_t)kWaves * 32 * 2 * 4;          // per wave m[32], l[32]
-  static constexpr size_t kMerge = (size_t)2 * kMaxSplits * kAttnMaxQ * 4;
-  static constexpr size_t kTotal = kMain + kML + (kMerge > kMain ? kMerge - kMain : 0);
+constexpr size_t attn_mfma_lds(int M) {
+  const size_t qp = (size_t)3 * M * DH * 2, vt = (size_t)(kWG / 64) * 32 * (DH * 2 + 16);
+  const size_t o = (size_t)(kWG / 64) * M * DH * 4;
+  return (qp + vt > o ? qp + vt : o) + (size_t)(kWG / 64) * 64 * 4;
+}
+
+// Rows at consecutive positions (a row block, or one stage's token).
+struct LimPos {
+  int pos0;
+  __device__ __forceinline__ int operator()(int r) const { return pos0 + r; }
 };
 
-template <int DH>
-constexpr size_t attn_rows_mfma_lds() {
-  return RowsMfmaLds<DH>::kTotal;
+// The page of the first key a lane reads of its wave's first tile.
+__device__ __forceinline__ int attn_mfma_page0(const Ctx& C, int split) {
+  const int key = split * C.chunk + (int)(threadIdx.x >> 6) * 32 + (int)(threadIdx.x & 31);
+  return C.page_table[min(key / C.page, C.max_pages - 1)];
 }
 
-// bf16 element e of a run of packed bf16 words, as fp32 (exact)
-template <int N>
-__device__ __forceinline__ float bf_at(const uint4 (&w)[N], int e) {
-  const uint4 v = w[e >> 3];
-  const int k = (e >> 1) & 3;
-  const uint32_t u = k == 0 ? v.x : k == 1 ? v.y : k == 2 ? v.z : v.w;
-  return (e & 1) ? bf_hi(u) : bf_lo(u);
-}
-
-// One key split [k0, k0 + chunk) of KV head g for the rows of a block. kvb: the layer's bf16 cache;
-// q, out: the block's query and output rows (row r at r * qdim, head g's G heads contiguous);
-// part, cnt: the split records and tickets of (row r, KV head g) at index r * hkv + g.
-template <int DH>
-__device__ void attn_rows_mfma(const Ctx& C, const uint16_t* kvb, const float* q, float* out, float* part, int* cnt,
-                               int g, int split, int nrows, int pos0, float* lds) {
-  constexpr int HALF = DH / 2, NT = DH / 32, KV16 = HALF / 8;  // dims per lane half, dim tiles, uint4 per run
-  constexpr int MAXQ = kAttnMaxQ, RS = MAXQ * (DH + 2);
-  using LA = RowsMfmaLds<DH>;
-  __shared__ int s_last[kMaxRows];
+// kvb: the layer's bf16 cache; q, out: query and output rows (row r at r * qdim, head g's G heads
+// contiguous); part: the split records of (row r, KV head g) at index r * hkv + g;
+// page0: attn_mfma_page0, requested by the caller; kend: the longest row's keys, [0, kend).
+template <int DH, typename Lim>
+__device__ void attn_split_mfma(const Ctx& C, const uint16_t* kvb, const float* q, float* out, float* part, int g,
+                                int split, int nrows, int kend, const Lim lim, int page0, float* lds) {
+  constexpr int NT = DH / 32, KS = DH / 16, KV16 = DH / 16;  // dim tiles, k steps of S, 16-byte loads per half row
+  constexpr int MAXQ = kAttnMaxQ, RS = MAXQ * (DH + 2), NWV = kWG / 64, VROW = DH * 2 + 16;
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
   const int col = lane & 31, hf = lane >> 5;
   const int G = C.G, M = nrows * G;
-  const int kend = pos0 + nrows;  // keys of the block: [0, kend)
   const int k0 = split * C.chunk, k1 = min(kend, k0 + C.chunk);
   char* const lbase = reinterpret_cast<char*>(lds);
-  char* const vt = lbase + (size_t)w * 32 * LA::kRow;  // this wave's V tile
+  char* const qpl = lbase;                                                  // [3][M][DH] bf16, chunks permuted
+  char* const vt = lbase + (size_t)3 * M * DH * 2 + (size_t)w * 32 * VROW;  // this wave's V tile
   const size_t page_elems = (size_t)2 * C.hkv * C.page * DH;
   const size_t head_off = (size_t)g * C.page * DH;
   const size_t voff = (size_t)C.hkv * C.page * DH;
-
-  // this lane's query: column col; row r = col / G, head h = col % G (columns >= M are zero)
-  const int qr = col / G, qh = col % G;
-  const bool qon = col < M;
-  const int qlim = pos0 + qr;  // last key the query attends
-  float qf[HALF];
-  {
-    const float* qp = q + (size_t)min(qr, nrows - 1) * C.qdim + (size_t)(g * G + qh) * DH + hf * HALF;
-#pragma unroll
-    for (int e = 0; e < HALF; e += 4) {
-      const float4 v = *reinterpret_cast<const float4*>(qp + e);
-      qf[e] = qon ? v.x * C.scale : 0.f;
-      qf[e + 1] = qon ? v.y * C.scale : 0.f;
-      qf[e + 2] = qon ? v.z * C.scale : 0.f;
-      qf[e + 3] = qon ? v.w * C.scale : 0.f;
-    }
-  }
   const int ntiles = (k1 - k0 + 31) / 32;
-  auto key_of = [&](int t) { return min(k0 + t * 32 + col, k1 - 1); };  // this lane's key of tile t (clamped)
+
+  // A lane reads its key of a tile as it comes: a key past the end lies in some page of the table, its
+  // score is masked and its V row enters the tile as zeros.
   uint4 kr[KV16], vr[KV16];
+  auto page_of = [&](int t) { return C.page_table[min((k0 + t * 32 + col) / C.page, C.max_pages - 1)]; };
   auto issue = [&](int t, int page) {
-    const int key = key_of(t);
-    const uint16_t* base = kvb + (size_t)page * page_elems + head_off + (size_t)(key % C.page) * DH + hf * HALF;
+    const int key = k0 + t * 32 + col;
+    const uint16_t* base = kvb + (size_t)page * page_elems + head_off + (size_t)(key % C.page) * DH + hf * 8;
 #pragma unroll
-    for (int c = 0; c < KV16; c++) kr[c] = ldkv16(reinterpret_cast<const uint4*>(base) + c);
+    for (int c = 0; c < KV16; c++) kr[c] = ldkv16(base + c * 16);
 #pragma unroll
-    for (int c = 0; c < KV16; c++) vr[c] = ldkv16(reinterpret_cast<const uint4*>(base + voff) + c);
+    for (int c = 0; c < KV16; c++) vr[c] = ldkv16(base + voff + c * 16);
   };
-  // every wave runs the same number of tile steps (a step past the split's tiles loads the last key
-  // and masks everything), so the MFMAs always run on full waves
-  const int steps = (ntiles + LA::kWaves - 1) / LA::kWaves;
   int t = w;
-  int pg_next = C.page_table[key_of(min(t + LA::kWaves, ntiles - 1)) / C.page];
-  issue(min(t, ntiles - 1), C.page_table[key_of(min(t, ntiles - 1)) / C.page]);
+  int pg_next = page_of(t + NWV);
+  issue(t, page0);
+
+  // query planes: thread e takes eight dims of a query
+  for (int e = tid; e < M * (DH / 8); e += kWG) {
+    const int j = e / (DH / 8), c = e % (DH / 8), r = j / G, h = j % G;
+    const float* qp = q + (size_t)r * C.qdim + (size_t)(g * G + h) * DH + c * 8;
+    const float4 a = *reinterpret_cast<const float4*>(qp), b = *reinterpret_cast<const float4*>(qp + 4);
+    const float f[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+    uint32_t pl[3][4];
+#pragma unroll
+    for (int k = 0; k < 8; k++) {
+      const float x = f[k] * C.scale;
+      const uint32_t hi = __float_as_uint(x);
+      const float r1 = x - __uint_as_float(hi & 0xffff0000u);
+      const uint32_t mi = __float_as_uint(r1);
+      const uint32_t lo = __float_as_uint(r1 - __uint_as_float(mi & 0xffff0000u));
+      if (k & 1) {
+        pl[0][k >> 1] |= hi & 0xffff0000u;
+        pl[1][k >> 1] |= mi & 0xffff0000u;
+        pl[2][k >> 1] |= lo & 0xffff0000u;
+      } else {
+        pl[0][k >> 1] = hi >> 16;
+        pl[1][k >> 1] = mi >> 16;
+        pl[2][k >> 1] = lo >> 16;
+      }
+    }
+#pragma unroll
+    for (int p = 0; p < 3; p++)
+      *reinterpret_cast<uint4*>(qpl + ((size_t)p * M + j) * DH * 2 + ((c ^ (j & 7)) << 4)) =
+          make_uint4(pl[p][0], pl[p][1], pl[p][2], pl[p][3]);
+  }
+  // this lane's query: column col; columns past M repeat one, and are not used
+  const bool qon = col < M;
+  const int qc = qon ? col : col % M;
+  const int qlim = lim(qc / G);
+  __syncthreads();  // queries staged
 
   float m_run = -INFINITY, l_run = 0.f;
   mfma_acc16 o[NT];
@@ -522,85 +540,109 @@ __device__ void attn_rows_mfma(const Ctx& C, const uint16_t* kvb, const float* q
 #pragma unroll
     for (int v = 0; v < 16; v++) o[tt][v] = 0.f;
 
-  for (int it = 0; it < steps; it++, t += LA::kWaves) {
-    const int kb = k0 + t * 32;  // the tile's first key (t past the end: nothing valid)
-    // V run of key col to the wave's tile
+  for (; t < ntiles; t += NWV) {
+    const int kb = k0 + t * 32;  // the tile's first key
+    const bool kin = kb + col < k1;
 #pragma unroll
-    for (int c = 0; c < KV16; c++) reinterpret_cast<uint4*>(vt + (size_t)col * LA::kRow + hf * HALF * 2)[c] = vr[c];
-    mfma_acc16 sacc;
+    for (int c = 0; c < KV16; c++)  // dims 16 c + 8 hf of key col
+      *reinterpret_cast<uint4*>(vt + (size_t)col * VROW + c * 32 + hf * 16) = kin ? vr[c] : make_uint4(0u, 0u, 0u, 0u);
+    mfma_acc16 s;
 #pragma unroll
-    for (int v = 0; v < 16; v++) sacc[v] = 0.f;
+    for (int v = 0; v < 16; v++) s[v] = 0.f;
 #pragma unroll
-    for (int kc = 0; kc < HALF; kc++) sacc = __builtin_amdgcn_mfma_f32_32x32x2f32(bf_at(kr, kc), qf[kc], sacc, 0, 0, 0);
-    {  // the registers are free again: the next tile, and the page of the one after
-      const int tn = min(t + LA::kWaves, ntiles - 1);
-      const int pg = pg_next;
-      pg_next = C.page_table[key_of(min(t + 2 * LA::kWaves, ntiles - 1)) / C.page];
-      issue(tn, pg);
+    for (int p = 2; p >= 0; p--)  // the small products first
+#pragma unroll
+      for (int k = 0; k < KS; k++) {
+        union { uint4 u; mfma_bf8 f; } ka;
+        ka.u = kr[k];
+        const mfma_bf8 qf = *reinterpret_cast<const mfma_bf8*>(qpl + ((size_t)p * M + qc) * DH * 2 +
+                                                               (((2 * k + hf) ^ (qc & 7)) << 4));
+        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka.f, qf, s, 0, 0, 0);
+      }
+    if (t + NWV < ntiles) {  // the registers are free again: the next tile, and the page of the one after
+      issue(t + NWV, pg_next);
+      pg_next = page_of(t + 2 * NWV);
     }
-    float p[16];
     float mx = -INFINITY;
 #pragma unroll
     for (int v = 0; v < 16; v++) {
       const int key = kb + 8 * (v >> 2) + 4 * hf + (v & 3);
-      const bool ok = qon && t < ntiles && key < k1 && key <= qlim;
-      p[v] = ok ? sacc[v] : -INFINITY;
-      mx = fmaxf(mx, p[v]);
+      s[v] = (key < k1 && key <= qlim) ? s[v] : -INFINITY;
+      mx = fmaxf(mx, s[v]);
     }
     mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
     const float mn = fmaxf(m_run, mx);
-    const float al = m_run == -INFINITY ? 0.f : expf(m_run - mn);
+    if (__any(mn > m_run)) {
+      const float al = m_run == -INFINITY ? 0.f : expf(m_run - mn);
+      l_run *= al;
+#pragma unroll
+      for (int tt = 0; tt < NT; tt++)
+#pragma unroll
+        for (int v = 0; v < 16; v++) o[tt][v] *= al;
+      m_run = mn;
+    }
+    wave_lds_sync();  // the V tile is written
     float ps = 0.f;
 #pragma unroll
-    for (int v = 0; v < 16; v++) {
-      p[v] = p[v] == -INFINITY ? 0.f : expf(p[v] - mn);
-      ps += p[v];
-    }
-    ps += __shfl_xor(ps, 32, 64);
-    l_run = l_run * al + ps;
-    m_run = mn;
+    for (int ks = 0; ks < 2; ks++) {
+      union { uint32_t u[4]; mfma_bf8 f; } pf[3];
 #pragma unroll
-    for (int tt = 0; tt < NT; tt++)
+      for (int e = 0; e < 8; e += 2) {
+        const float s0 = s[8 * ks + e], s1 = s[8 * ks + e + 1];
+        const float p0 = s0 == -INFINITY ? 0.f : expf(s0 - m_run), p1 = s1 == -INFINITY ? 0.f : expf(s1 - m_run);
+        ps += p0 + p1;
+        const uint32_t h0 = __float_as_uint(p0), h1 = __float_as_uint(p1);
+        const float r0 = p0 - __uint_as_float(h0 & 0xffff0000u), r1 = p1 - __uint_as_float(h1 & 0xffff0000u);
+        const uint32_t m0 = __float_as_uint(r0), m1 = __float_as_uint(r1);
+        const uint32_t l0 = __float_as_uint(r0 - __uint_as_float(m0 & 0xffff0000u));
+        const uint32_t l1 = __float_as_uint(r1 - __uint_as_float(m1 & 0xffff0000u));
+        pf[0].u[e >> 1] = __builtin_amdgcn_perm(h1, h0, 0x07060302u);
+        pf[1].u[e >> 1] = __builtin_amdgcn_perm(m1, m0, 0x07060302u);
+        pf[2].u[e >> 1] = __builtin_amdgcn_perm(l1, l0, 0x07060302u);
+      }
+      uint32_t vw[8][NT / 2];  // the eight keys' NT dims of this lane's row
 #pragma unroll
-      for (int v = 0; v < 16; v++) o[tt][v] *= al;
-    wave_lds_sync();  // the V tile is written
-#pragma unroll
-    for (int v = 0; v < 16; v++) {
-      const int kr_ = 8 * (v >> 2) + 4 * hf + (v & 3);  // the key of register v on this lane half
-      const char* vp = vt + (size_t)kr_ * LA::kRow + col * NT * 2;
-      float a[NT];
-      if constexpr (NT == 4) {
-        const uint2 u = *reinterpret_cast<const uint2*>(vp);
-        a[0] = bf_lo(u.x);
-        a[1] = bf_hi(u.x);
-        a[2] = bf_lo(u.y);
-        a[3] = bf_hi(u.y);
-      } else {
-        const uint32_t u = *reinterpret_cast<const uint32_t*>(vp);
-        a[0] = bf_lo(u);
-        a[1] = bf_hi(u);
+      for (int e = 0; e < 8; e++) {
+        const char* vp = vt + (size_t)(16 * ks + 8 * (e >> 2) + 4 * hf + (e & 3)) * VROW + col * NT * 2;
+        if constexpr (NT == 4) {
+          const uint2 u = *reinterpret_cast<const uint2*>(vp);
+          vw[e][0] = u.x;
+          vw[e][1] = u.y;
+        } else {
+          vw[e][0] = *reinterpret_cast<const uint32_t*>(vp);
+        }
       }
 #pragma unroll
-      for (int tt = 0; tt < NT; tt++) o[tt] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[tt], p[v], o[tt], 0, 0, 0);
+      for (int tt = 0; tt < NT; tt++) {
+        union { uint32_t u[4]; mfma_bf8 f; } va;
+        const uint32_t sel = (tt & 1) ? 0x07060302u : 0x05040100u;
+#pragma unroll
+        for (int e = 0; e < 4; e++) va.u[e] = __builtin_amdgcn_perm(vw[2 * e + 1][tt >> 1], vw[2 * e][tt >> 1], sel);
+#pragma unroll
+        for (int p = 2; p >= 0; p--) o[tt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va.f, pf[p].f, o[tt], 0, 0, 0);
+      }
     }
+    l_run += ps + __shfl_xor(ps, 32, 64);
     wave_lds_sync();  // the tile is rewritten next step
   }
-  __syncthreads();  // every wave is done with its V tile: the area holds the waves' o now
+  __syncthreads();  // every wave is done with the planes and its V tile: the area holds the waves' o now
 
-  // the wave's (m, l, o) to LDS: o[query][dim], dims 16-row block by block
-  float* ow = reinterpret_cast<float*>(lbase) + (size_t)w * 32 * DH;
-  float* mlw = reinterpret_cast<float*>(lbase + LA::kMain) + (size_t)w * 64;
+  float* ow = reinterpret_cast<float*>(lbase) + (size_t)w * M * DH;  // o[query][dim]
+  const size_t main_bytes = attn_mfma_lds<DH>(M) - (size_t)NWV * 64 * 4;
+  float* mlw = reinterpret_cast<float*>(lbase + main_bytes) + (size_t)w * 64;
   if (hf == 0) {
     mlw[col] = m_run;
     mlw[32 + col] = l_run;
   }
+  if (qon) {
 #pragma unroll
-  for (int v = 0; v < 16; v++) {
-    const int i = 8 * (v >> 2) + 4 * hf + (v & 3);
-    if constexpr (NT == 4) {
-      *reinterpret_cast<float4*>(ow + (size_t)col * DH + i * 4) = make_float4(o[0][v], o[1][v], o[2][v], o[3][v]);
-    } else {
-      *reinterpret_cast<float2*>(ow + (size_t)col * DH + i * 2) = make_float2(o[0][v], o[1][v]);
+    for (int v = 0; v < 16; v++) {
+      const int i = 8 * (v >> 2) + 4 * hf + (v & 3);
+      if constexpr (NT == 4) {
+        *reinterpret_cast<float4*>(ow + (size_t)col * DH + i * 4) = make_float4(o[0][v], o[1][v], o[2][v], o[3][v]);
+      } else {
+        *reinterpret_cast<float2*>(ow + (size_t)col * DH + i * 2) = make_float2(o[0][v], o[1][v]);
+      }
     }
   }
   __syncthreads();
@@ -608,64 +650,51 @@ __device__ void attn_rows_mfma(const Ctx& C, const uint16_t* kvb, const float* q
   // combine the waves in wave order per (query, dim pair); write a one-split row's output, else the
   // row's split record. A query of a row that has keys in this split has a valid key in wave 0's
   // first tile (key k0), so M is finite.
-  constexpr int NPAIR = 32 * DH / 2, PPT = NPAIR / kWG;
-  const float* mlb = reinterpret_cast<const float*>(lbase + LA::kMain);
-#pragma unroll
-  for (int i = 0; i < PPT; i++) {
-    const int e = tid + i * kWG, j = e / (DH / 2), dp = e % (DH / 2);
+  const float* mlb = reinterpret_cast<const float*>(lbase + main_bytes);
+  for (int e = tid; e < M * (DH / 2); e += kWG) {
+    const int j = e / (DH / 2), dp = e % (DH / 2);
     const int r = j / G, h = j % G;
-    if (j >= M || k0 > pos0 + r) continue;  // no query, or no key of this split for the row
+    if (k0 > lim(r)) continue;  // no key of this split for the row
     float Mx = -INFINITY;
 #pragma unroll
-    for (int wv = 0; wv < LA::kWaves; wv++) Mx = fmaxf(Mx, mlb[wv * 64 + j]);
+    for (int wv = 0; wv < NWV; wv++) Mx = fmaxf(Mx, mlb[wv * 64 + j]);
     float L = 0.f, a0 = 0.f, a1 = 0.f;
 #pragma unroll
-    for (int wv = 0; wv < LA::kWaves; wv++) {
+    for (int wv = 0; wv < NWV; wv++) {
       const float mw = mlb[wv * 64 + j];
       if (mw != -INFINITY) {
         const float f = expf(mw - Mx);
         L = fmaf(mlb[wv * 64 + 32 + j], f, L);
         const float2 ov = *reinterpret_cast<const float2*>(reinterpret_cast<const float*>(lbase) +
-                                                           ((size_t)wv * 32 + j) * DH + 2 * dp);
+                                                           ((size_t)wv * M + j) * DH + 2 * dp);
         a0 = fmaf(ov.x, f, a0);
         a1 = fmaf(ov.y, f, a1);
       }
     }
-    const int nsplit = (pos0 + r + C.chunk) / C.chunk;
+    const int nsplit = (lim(r) + C.chunk) / C.chunk;
     if (nsplit == 1) {
       const float inv = 1.0f / L;
       *reinterpret_cast<float2*>(out + (size_t)r * C.qdim + (size_t)(g * G + h) * DH + 2 * dp) =
           make_float2(a0 * inv, a1 * inv);
     } else {
       float* rec = part + ((size_t)(r * C.hkv + g) * C.max_splits + split) * RS;
-      st_dev2f(rec + h * DH + 2 * dp, a0, a1);
+      *reinterpret_cast<float2*>(rec + h * DH + 2 * dp) = make_float2(a0, a1);
       if (dp == 0) {
-        st_dev(rec + MAXQ * DH + h, Mx);
-        st_dev(rec + MAXQ * DH + MAXQ + h, L);
+        rec[MAXQ * DH + h] = Mx;
+        rec[MAXQ * DH + MAXQ + h] = L;
       }
     }
   }
-  wait_own_stores();
-  __syncthreads();
-  if (tid < nrows) {
-    const int r = tid, nsplit = (pos0 + r + C.chunk) / C.chunk;
-    int last = 0;
-    if (nsplit > 1 && split < nsplit) {
-      const int tk = __hip_atomic_fetch_add(cnt + r * C.hkv + g, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      last = tk == nsplit - 1;
-    }
-    s_last[r] = last;
-  }
-  __syncthreads();
-  float* sm = reinterpret_cast<float*>(lbase);  // the merge's (m, l) staging (the wave areas are free)
-  for (int r = 0; r < nrows; r++) {
-    if (!s_last[r]) continue;  // workgroup-uniform
-    const int nsplit = (pos0 + r + C.chunk) / C.chunk;
-    attn_merge<DH>(part + (size_t)(r * C.hkv + g) * C.max_splits * RS, nsplit, G,
-                   out + (size_t)r * C.qdim + (size_t)g * G * DH, sm);
-    if (tid == 0) __hip_atomic_store(cnt + r * C.hkv + g, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __syncthreads();  // the staging area is reused by the next row's merge
-  }
+}
+
+// Row r's KV head g of a split launch: merges its split records (nothing to do if it has one split).
+template <int DH>
+__device__ __forceinline__ void attn_merge_row(const Ctx& C, const float* part, float* out, int r, int g, int len,
+                                               float* sm) {
+  const int nsplit = (len + C.chunk - 1) / C.chunk;
+  if (nsplit > 1)
+    attn_merge<DH, false>(part + (size_t)(r * C.hkv + g) * C.max_splits * kAttnMaxQ * (DH + 2), nsplit, C.G,
+                          out + (size_t)r * C.qdim + (size_t)g * C.G * DH, sm);
 }
 
 // One split. kvb: the layer's

@@ -44,6 +44,38 @@ __global__ __launch_bounds__(kWG) void k_attn_ragged(Ctx C, const float* q, cons
                             nsplit, k0, k1, len - 1, page0, lds);
 }
 
+// bf16 pools: rows of one KV head share its pages, so a workgroup serves 32 / G rows of a (key split, KV
+// head) on matrix cores. Grid: x = key split, y = KV head, z = row group.
+struct LimLens {
+  const int* lens;
+  __device__ __forceinline__ int operator()(int r) const { return lens[r] - 1; }
+};
+
+template <int DH>
+__global__ __launch_bounds__(kWG, 2) void k_attn_ragged_mfma(Ctx C, const float* q, const uint16_t* kv, float* out,
+                                                          float* part, RaggedRows R, int nrows) {
+  extern __shared__ __align__(16) float lds[];
+  __shared__ int s_lens[kMaxRows];
+  const int rpg = 32 / C.G, r0 = blockIdx.z * rpg, nr = min(rpg, nrows - r0), split = blockIdx.x;
+  int kend = 0;
+  for (int i = 0; i < nr; i++) kend = max(kend, R.lens[r0 + i]);
+  if (split * C.chunk >= kend) return;
+  const int page0 = attn_mfma_page0(C, split);
+  if (threadIdx.x < nr) s_lens[threadIdx.x] = R.lens[r0 + threadIdx.x];
+  __syncthreads();
+  const size_t rec0 = (size_t)r0 * C.hkv;
+  attn_split_mfma<DH>(C, kv, q + (size_t)r0 * C.qdim, out + (size_t)r0 * C.qdim,
+                      part + rec0 * C.max_splits * (kAttnMaxQ * (DH + 2)), blockIdx.y, split, nr, kend,
+                      LimLens{s_lens}, page0, lds);
+}
+
+// The rows' split records into their outputs. Grid: x = KV head, y = row.
+template <int DH>
+__global__ __launch_bounds__(kWG) void k_attn_ragged_merge(Ctx C, float* out, const float* part, RaggedRows R) {
+  __shared__ __align__(16) float sm[2 * kMaxSplits * kAttnMaxQ];
+  attn_merge_row<DH>(C, part, out, blockIdx.y, blockIdx.x, R.lens[blockIdx.y], sm);
+}
+
 __global__ __launch_bounds__(kWG) void k_zero_i32(int* p, int n) {
   for (int i = blockIdx.x * kWG + threadIdx.x; i < n; i += gridDim.x * kWG) p[i] = 0;
 }
@@ -107,33 +139,45 @@ spd_status check(const float* q, const void* kv, const int32_t* page_table, int3
   return SPD_OK;
 }
 
-template <typename KVT, int DH>
-void launch_ragged(const Request& r, const float* q, const void* kv, float* out, float* part, int* cnt,
-                   hipStream_t s) {
+template <int DH>
+void launch_ragged_f32(const Request& r, const float* q, const void* kv, float* out, float* part, int* cnt,
+                       hipStream_t s) {
   const dim3 grid(r.smax, r.C.hkv, r.nrows);
-  const size_t shm = attn_split_lds<KVT, DH>();
+  const size_t shm = attn_split_lds<float, DH>();
   if (r.g4)
-    hipLaunchKernelGGL((k_attn_ragged<KVT, DH, 4>), grid, dim3(kWG), shm, s, r.C, q, (const KVT*)kv, out, part, cnt,
+    hipLaunchKernelGGL((k_attn_ragged<float, DH, 4>), grid, dim3(kWG), shm, s, r.C, q, (const float*)kv, out, part, cnt,
                        r.R, r.smax);
   else
-    hipLaunchKernelGGL((k_attn_ragged<KVT, DH, 8>), grid, dim3(kWG), shm, s, r.C, q, (const KVT*)kv, out, part, cnt,
+    hipLaunchKernelGGL((k_attn_ragged<float, DH, 8>), grid, dim3(kWG), shm, s, r.C, q, (const float*)kv, out, part, cnt,
                        r.R, r.smax);
 }
 
-// Clears the tickets (a fill kernel, so that a captured call replays correctly), then the attention.
+template <int DH>
+void launch_ragged_bf16(const Request& r, const float* q, const void* kv, float* out, float* part, hipStream_t s) {
+  const int rpg = 32 / r.C.G;
+  const dim3 grid(r.smax, r.C.hkv, (r.nrows + rpg - 1) / rpg);
+  hipLaunchKernelGGL((k_attn_ragged_mfma<DH>), grid, dim3(kWG), attn_mfma_lds<DH>(std::min(r.nrows, rpg) * r.C.G), s, r.C,
+                     q, (const uint16_t*)kv, out, part, r.R, r.nrows);
+  if (r.smax > 1)
+    hipLaunchKernelGGL((k_attn_ragged_merge<DH>), dim3(r.C.hkv, r.nrows), dim3(kWG), 0, s, r.C, out,
+                       (const float*)part, r.R);
+}
+
+// bf16: the splits, then (with more than one) their merge. fp32: the tickets are cleared (a fill kernel,
+// so that a captured call replays correctly), then the attention, whose last splits merge.
 spd_status run(const Request& r, const float* q, const void* kv, float* out, float* part, int* cnt, void* stream) {
   hipStream_t s = (hipStream_t)stream;
-  hipLaunchKernelGGL(k_zero_i32, dim3((r.tickets + kWG - 1) / kWG), dim3(kWG), 0, s, cnt, r.tickets);
   if (r.bf16) {
     if (r.dh == 128)
-      launch_ragged<uint16_t, 128>(r, q, kv, out, part, cnt, s);
+      launch_ragged_bf16<128>(r, q, kv, out, part, s);
     else
-      launch_ragged<uint16_t, 64>(r, q, kv, out, part, cnt, s);
+      launch_ragged_bf16<64>(r, q, kv, out, part, s);
   } else {
+    hipLaunchKernelGGL(k_zero_i32, dim3((r.tickets + kWG - 1) / kWG), dim3(kWG), 0, s, cnt, r.tickets);
     if (r.dh == 128)
-      launch_ragged<float, 128>(r, q, kv, out, part, cnt, s);
+      launch_ragged_f32<128>(r, q, kv, out, part, cnt, s);
     else
-      launch_ragged<float, 64>(r, q, kv, out, part, cnt, s);
+      launch_ragged_f32<64>(r, q, kv, out, part, cnt, s);
   }
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) {

@@ -940,20 +940,33 @@ __global__ __launch_bounds__(kWG) void k_attn_rows(Ctx C, Rows R, int nrg) {
                                    k1, pos0, page0, lds);
 }
 
-// Row-block attention on matrix cores (bf16 caches, rows * G <= 32 queries): one workgroup per (key
-// split, KV head) serves every row of the block (attn_rows_mfma). Grid: x = key split, y = KV head;
-// splits past the block's last key return at once.
+// Row-block attention of bf16 caches on matrix cores: one workgroup per (key split, KV head, group of
+// 32 / G rows) serves every query of its rows (attn_split_mfma). Grid: x = key split, y = KV head,
+// z = row group; splits past the group's last key return at once.
 template <int DH>
-__global__ __launch_bounds__(kWG) void k_attn_rows_mfma(Ctx C, Rows R) {
+__global__ __launch_bounds__(kWG, 2) void k_attn_rows_mfma(Ctx C, Rows R) {
   extern __shared__ __align__(16) float lds[];
   const Grp gr = resolve(C, R, 0);
-  if (!gr.active) return;
-  const int split = blockIdx.x, g = blockIdx.y;
-  if (split * C.chunk >= gr.pos0 + gr.nrows) return;
+  const int rpg = 32 / C.G, r0 = blockIdx.z * rpg;
+  if (!gr.active || r0 >= gr.nrows) return;
+  const int split = blockIdx.x, g = blockIdx.y, nr = min(rpg, gr.nrows - r0), pos0 = gr.pos0 + r0;
+  if (split * C.chunk >= pos0 + nr) return;
   const BufSet& B = C.b[R.set];
-  const size_t row0 = (size_t)gr.brow0 * C.qdim;
-  attn_rows_mfma<DH>(C, (const uint16_t*)C.lay[gr.layer].kv, B.q + row0, B.ao + row0, B.part, B.cnt, g, split,
-                     gr.nrows, gr.pos0, lds);
+  const size_t row0 = (size_t)(gr.brow0 + r0) * C.qdim, rec0 = (size_t)r0 * C.hkv;
+  attn_split_mfma<DH>(C, (const uint16_t*)C.lay[gr.layer].kv, B.q + row0, B.ao + row0,
+                      B.part + rec0 * C.max_splits * (kAttnMaxQ * (DH + 2)), g, split, nr, pos0 + nr, LimPos{pos0},
+                      attn_mfma_page0(C, split), lds);
+}
+
+// The rows' split records into their outputs. Grid: x = KV head, y = row.
+template <int DH>
+__global__ __launch_bounds__(kWG) void k_attn_rows_merge(Ctx C, Rows R) {
+  __shared__ __align__(16) float sm[2 * kMaxSplits * kAttnMaxQ];
+  const Grp gr = resolve(C, R, 0);
+  const int r = blockIdx.y;
+  if (!gr.active || r >= gr.nrows) return;
+  const BufSet& B = C.b[R.set];
+  attn_merge_row<DH>(C, B.part, B.ao + (size_t)gr.brow0 * C.qdim, r, blockIdx.x, gr.pos0 + r + 1, sm);
 }
 
 // Launch trace reset.
@@ -1459,28 +1472,30 @@ void Launch<WT>::rows_sublayer(const Ctx& c, const Rows& r, int max_rows, int k,
   if (k == 4) rgemv_launch<WT, SG_DOWN>(c, r, (c.d + 1) / 2, c.F, max_rows, cap_wgs, s);
   if (k != 1) return;
   if constexpr (std::is_same<WT, uint16_t>::value) {
-    if (max_rows * c.G <= 32 && (c.dh == 64 || c.dh == 128)) {  // every query of the block in one MFMA tile
-      const dim3 grid(c.max_splits, c.hkv);
-      if (c.dh == 128)
-        launch_timed((k_attn_rows_mfma<128>), grid, dim3(kWG), attn_rows_mfma_lds<128>(), S(s), c, r);
-      else
-        launch_timed((k_attn_rows_mfma<64>), grid, dim3(kWG), attn_rows_mfma_lds<64>(), S(s), c, r);
-      return;
+    const int rpg = 32 / c.G, M = std::min(max_rows, rpg) * c.G;
+    const dim3 grid(c.max_splits, c.hkv, (max_rows + rpg - 1) / rpg), mgrid(c.hkv, max_rows);
+    if (c.dh == 128) {
+      launch_timed((k_attn_rows_mfma<128>), grid, dim3(kWG), attn_mfma_lds<128>(M), S(s), c, r);
+      if (c.max_splits > 1) launch_timed((k_attn_rows_merge<128>), mgrid, dim3(kWG), 0, S(s), c, r);
+    } else {
+      launch_timed((k_attn_rows_mfma<64>), grid, dim3(kWG), attn_mfma_lds<64>(M), S(s), c, r);
+      if (c.max_splits > 1) launch_timed((k_attn_rows_merge<64>), mgrid, dim3(kWG), 0, S(s), c, r);
     }
-  }
-  const int groups8 = (c.max_splits * c.hkv + 7) / 8 * 8;  // see k_attn_rows: XCD-aware order
-  const dim3 agrid(groups8 * max_rows);
-  const bool g4 = c.G <= 4;
-  if (c.dh == 128) {
-    if (g4)
-      launch_timed((k_attn_rows<WT, 128, 4>), agrid, dim3(kWG), attn_split_lds<WT, 128>(), S(s), c, r, max_rows);
-    else
-      launch_timed((k_attn_rows<WT, 128, 8>), agrid, dim3(kWG), attn_split_lds<WT, 128>(), S(s), c, r, max_rows);
   } else {
-    if (g4)
-      launch_timed((k_attn_rows<WT, 64, 4>), agrid, dim3(kWG), attn_split_lds<WT, 64>(), S(s), c, r, max_rows);
-    else
-      launch_timed((k_attn_rows<WT, 64, 8>), agrid, dim3(kWG), attn_split_lds<WT, 64>(), S(s), c, r, max_rows);
+    const int groups8 = (c.max_splits * c.hkv + 7) / 8 * 8;  // see k_attn_rows: XCD-aware order
+    const dim3 agrid(groups8 * max_rows);
+    const bool g4 = c.G <= 4;
+    if (c.dh == 128) {
+      if (g4)
+        launch_timed((k_attn_rows<WT, 128, 4>), agrid, dim3(kWG), attn_split_lds<WT, 128>(), S(s), c, r, max_rows);
+      else
+        launch_timed((k_attn_rows<WT, 128, 8>), agrid, dim3(kWG), attn_split_lds<WT, 128>(), S(s), c, r, max_rows);
+    } else {
+      if (g4)
+        launch_timed((k_attn_rows<WT, 64, 4>), agrid, dim3(kWG), attn_split_lds<WT, 64>(), S(s), c, r, max_rows);
+      else
+        launch_timed((k_attn_rows<WT, 64, 8>), agrid, dim3(kWG), attn_split_lds<WT, 64>(), S(s), c, r, max_rows);
+    }
   }
 }
 
