@@ -9,6 +9,7 @@
 #include <new>
 #include <random>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "spd.h"
@@ -274,10 +275,12 @@ static void enqueue_layer(const Ctx& C, const Rows& r, hipStream_t s, spd_handle
   { TimedLaunch t(h, s, SPD_K_DOWN); Launch<WT>::down(C, r, s); }
 }
 
-// PDM GEMV workgroups: kRowsWGsDefault per 256 MB of PDM weights (feature projection and decoder
-// layers), so that a larger draft module keeps finishing inside the stage compute.
+// PDM GEMV workgroups. fp32: kRowsWGsDefault per 256 MB of PDM weights (feature projection and decoder
+// layers), so that a larger draft module keeps finishing inside the stage compute. bf16: no cap (each
+// launch is short and streams near the memory's rate).
 static int default_rows_wgs(const spd_config& c) {
-  const double esz = c.dtype == SPD_BF16 ? 2.0 : 4.0;
+  if (c.dtype == SPD_BF16) return 0;
+  const double esz = 4.0;
   const double d = c.d_model, qd = (double)c.n_q_heads * c.head_dim, kvd = (double)c.n_kv_heads * c.head_dim;
   const double layer = d * (qd + 2 * kvd) + qd * d + 3 * d * c.ffn_dim;
   const double bytes = esz * (d * c.n_stages * d + c.pdm_layers * layer);
@@ -324,13 +327,17 @@ static spd_status enqueue_step(spd_handle* h, int forced_override) {
   const bool fused = h->cfg.fused_head != 0;
   // Pipeline Draft Module: pre-step features only (Section 3.3), so it can run beside the stage
   // compute; it ends by recording ev_join, which the LM head waits for. Its launches, in order: the
-  // feature projection, five per PDM layer, the draft head if not fused.
+  // feature projection, the PDM layers, the draft head if not fused.
   auto enqueue_pdm = [&](hipStream_t s) -> spd_status {
     h->cur_slot = 0;
-    Launch<WT>::pdm_fc(C, 0, 0, s);
-    for (int l = 0; l < h->cfg.pdm_layers; l++)
-      Launch<WT>::rows_layer(C, rows_block(h->cfg.n_layers + l, -1, -1, C.pdm_x, nullptr, -1, 1),
-                             h->cfg.n_stages, C.rows_wgs, s);
+    if constexpr (std::is_same<WT, uint16_t>::value) {
+      pdm_rows_mfma(C, h->pf, h->layer_desc.data(), h->cfg.n_stages, C.rows_wgs, s);
+    } else {
+      RowsF32::pdm_fc(C, 0, 0, s);
+      for (int l = 0; l < h->cfg.pdm_layers; l++)
+        RowsF32::layer(C, rows_block(h->cfg.n_layers + l, -1, -1, C.pdm_x, nullptr, -1, 1), h->cfg.n_stages,
+                       C.rows_wgs, s);
+    }
     if (!fused) {
       if (C.sam.top_k > 0)  // the draft module's distribution, left for the exit row's pass
         Launch<WT>::head_sample(C, 1, 0, 0, -1, 0, s);
@@ -465,17 +472,17 @@ static spd_status enqueue_prefill_f32(spd_handle* h, int len) {
   const int n = h->cfg.n_stages, L = h->cfg.n_layers;
   for (int t0 = 0; t0 < len; t0 += kMaxRows) {
     const int rc = std::min(kMaxRows, len - t0);
-    Launch<WT>::embed_rows(C, t0, rc, h->main);
+    RowsF32::embed(C, t0, rc, h->main);
     for (int l = 0; l < L; l++) {
       int cap = -1;
       for (int s = 0; s + 1 <= n - 1; s++)
         if (l + 1 == C.beta[s + 1]) cap = s + 1;
-      Launch<WT>::rows_layer(C, rows_block(l, rc, t0, C.pf_x, C.pf_anch, cap, 0), kMaxRows, 0, h->main);
+      RowsF32::layer(C, rows_block(l, rc, t0, C.pf_x, C.pf_anch, cap, 0), kMaxRows, 0, h->main);
     }
     // PDM KV over the prompt: every prompt row has full depth
-    Launch<WT>::pdm_fc(C, 1, rc, h->main);
+    RowsF32::pdm_fc(C, 1, rc, h->main);
     for (int i = 0; i < h->cfg.pdm_layers; i++)
-      Launch<WT>::rows_layer(C, rows_block(L + i, rc, t0, C.pdm_x, nullptr, -1, 1), kMaxRows, 0, h->main);
+      RowsF32::layer(C, rows_block(L + i, rc, t0, C.pdm_x, nullptr, -1, 1), kMaxRows, 0, h->main);
     if (t0 + rc == len) enqueue_first_token<WT>(h, rc - 1, len);
     spd_status st = launch_check(h, "prefill");
     if (st != SPD_OK) return st;

@@ -107,14 +107,28 @@ __device__ __forceinline__ void lds_row(const T* p, float* o) {
   }
 }
 
+// Where an attention writes its output: two consecutive values at an (even) element offset.
+struct FloatOut {
+  float* p;
+  __device__ __forceinline__ void operator()(size_t at, float a, float b) const {
+    *reinterpret_cast<float2*>(p + at) = make_float2(a, b);
+  }
+};
+template <typename Out>
+struct ShiftedOut {  // Out, from an element offset on
+  Out out;
+  size_t base;
+  __device__ __forceinline__ void operator()(size_t at, float a, float b) const { out(base + at, a, b); }
+};
+
 // Merge of one (token, KV head)'s nsplit split records (o[8][DH], m[8], l[8]; every split has a key,
 // so each m is finite) in split order into its G output rows. Every thread of the workgroup calls it.
 // All (m, l) pairs are requested first, then the first batch of partial outputs (only the entries
 // that exist: the records are read past the L2, where a repeated address costs as much as a new
 // one), then the (m, l) pairs go to LDS (sm: 2 * kMaxSplits * kAttnMaxQ floats). DEV: the records come
 // from workgroups of the same launch (device-scope loads); else from an earlier launch.
-template <int DH, bool DEV = true>
-__device__ __forceinline__ void attn_merge(const float* rec_base, int nsplit, int G, float* out, float* sm) {
+template <int DH, bool DEV, typename Out>
+__device__ __forceinline__ void attn_merge(const float* rec_base, int nsplit, int G, const Out out, float* sm) {
   constexpr int MAXQ = kAttnMaxQ, RS = MAXQ * (DH + 2);
   constexpr int NPAIR = MAXQ * DH / 2;
   constexpr int PPT = (NPAIR + kWG - 1) / kWG;
@@ -173,7 +187,7 @@ __device__ __forceinline__ void attn_merge(const float* rec_base, int nsplit, in
         }
       }
       const float inv = 1.0f / L;
-      *reinterpret_cast<float2*>(out + qi * DH + 2 * dp) = make_float2(a0 * inv, a1 * inv);
+      out((size_t)qi * DH + 2 * dp, a0 * inv, a1 * inv);
     }
   }
 }
@@ -410,7 +424,7 @@ __device__ bool attn_split_g(const Ctx& C, const KVT* kvb, const float* q, float
   __syncthreads();
   if (!s_last) return false;
 
-  attn_merge<DH>(rec_base, nsplit, G, out, reinterpret_cast<float*>(lbase + LA::kQ));
+  attn_merge<DH, true>(rec_base, nsplit, G, FloatOut{out}, reinterpret_cast<float*>(lbase + LA::kQ));
   if (tid == 0) __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   return true;
 }
@@ -465,8 +479,8 @@ __device__ __forceinline__ int attn_mfma_page0(const Ctx& C, int split) {
 // kvb: the layer's bf16 cache; q, out: query and output rows (row r at r * qdim, head g's G heads
 // contiguous); part: the split records of (row r, KV head g) at index r * hkv + g;
 // page0: attn_mfma_page0, requested by the caller; kend: the longest row's keys, [0, kend).
-template <int DH, typename Lim>
-__device__ void attn_split_mfma(const Ctx& C, const uint16_t* kvb, const float* q, float* out, float* part, int g,
+template <int DH, typename Out, typename Lim>
+__device__ void attn_split_mfma(const Ctx& C, const uint16_t* kvb, const float* q, const Out out, float* part, int g,
                                 int split, int nrows, int kend, const Lim lim, int page0, float* lds) {
   constexpr int NT = DH / 32, KS = DH / 16, KV16 = DH / 16;  // dim tiles, k steps of S, 16-byte loads per half row
   constexpr int MAXQ = kAttnMaxQ, RS = MAXQ * (DH + 2), NWV = kWG / 64, VROW = DH * 2 + 16;
@@ -674,8 +688,7 @@ __device__ void attn_split_mfma(const Ctx& C, const uint16_t* kvb, const float* 
     const int nsplit = (lim(r) + C.chunk) / C.chunk;
     if (nsplit == 1) {
       const float inv = 1.0f / L;
-      *reinterpret_cast<float2*>(out + (size_t)r * C.qdim + (size_t)(g * G + h) * DH + 2 * dp) =
-          make_float2(a0 * inv, a1 * inv);
+      out((size_t)r * C.qdim + (size_t)(g * G + h) * DH + 2 * dp, a0 * inv, a1 * inv);
     } else {
       float* rec = part + ((size_t)(r * C.hkv + g) * C.max_splits + split) * RS;
       *reinterpret_cast<float2*>(rec + h * DH + 2 * dp) = make_float2(a0, a1);
@@ -688,13 +701,13 @@ __device__ void attn_split_mfma(const Ctx& C, const uint16_t* kvb, const float* 
 }
 
 // Row r's KV head g of a split launch: merges its split records (nothing to do if it has one split).
-template <int DH>
-__device__ __forceinline__ void attn_merge_row(const Ctx& C, const float* part, float* out, int r, int g, int len,
+template <int DH, typename Out>
+__device__ __forceinline__ void attn_merge_row(const Ctx& C, const float* part, const Out out, int r, int g, int len,
                                                float* sm) {
   const int nsplit = (len + C.chunk - 1) / C.chunk;
   if (nsplit > 1)
     attn_merge<DH, false>(part + (size_t)(r * C.hkv + g) * C.max_splits * kAttnMaxQ * (DH + 2), nsplit, C.G,
-                          out + (size_t)r * C.qdim + (size_t)g * C.G * DH, sm);
+                          ShiftedOut<Out>{out, (size_t)r * C.qdim + (size_t)g * C.G * DH}, sm);
 }
 
 // One split. kvb: the layer's

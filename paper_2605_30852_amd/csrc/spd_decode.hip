@@ -64,7 +64,7 @@ __global__ __launch_bounds__(kWG, 2) void k_attn_ragged_mfma(Ctx C, const float*
   if (threadIdx.x < nr) s_lens[threadIdx.x] = R.lens[r0 + threadIdx.x];
   __syncthreads();
   const size_t rec0 = (size_t)r0 * C.hkv;
-  attn_split_mfma<DH>(C, kv, q + (size_t)r0 * C.qdim, out + (size_t)r0 * C.qdim,
+  attn_split_mfma<DH>(C, kv, q + (size_t)r0 * C.qdim, FloatOut{out + (size_t)r0 * C.qdim},
                       part + rec0 * C.max_splits * (kAttnMaxQ * (DH + 2)), blockIdx.y, split, nr, kend,
                       LimLens{s_lens}, page0, lds);
 }
@@ -73,7 +73,7 @@ __global__ __launch_bounds__(kWG, 2) void k_attn_ragged_mfma(Ctx C, const float*
 template <int DH>
 __global__ __launch_bounds__(kWG) void k_attn_ragged_merge(Ctx C, float* out, const float* part, RaggedRows R) {
   __shared__ __align__(16) float sm[2 * kMaxSplits * kAttnMaxQ];
-  attn_merge_row<DH>(C, part, out, blockIdx.y, blockIdx.x, R.lens[blockIdx.y], sm);
+  attn_merge_row<DH>(C, part, FloatOut{out}, blockIdx.y, blockIdx.x, R.lens[blockIdx.y], sm);
 }
 
 __global__ __launch_bounds__(kWG) void k_zero_i32(int* p, int n) {

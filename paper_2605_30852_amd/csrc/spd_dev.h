@@ -56,8 +56,8 @@ struct BufSet {
   float* act;       // [8][F] SwiGLU activations
   float* part;      // attention split partials
   int32_t* cnt;     // per (stage, KV head) split tickets of the decode attention; zero at rest
-  float* rpart;     // K-split row GEMV records (chunk dot products, sums of squares)
-  int32_t* rtick;   // K-split row GEMV tickets, one per workgroup column; zero at rest
+  float* rpart;     // fp32: K-split row GEMV records (chunk dot products, sums of squares)
+  int32_t* rtick;   // fp32: K-split row GEMV tickets, one per workgroup column; zero at rest
   // LM-head argmax of this stream's row: the maximum over the vocabulary of a 64-bit key that
   // orders (logit descending, index ascending); zero at rest (reset by its reader)
   unsigned long long* hkey;
@@ -70,7 +70,7 @@ enum StepKind { SK_QKV = 0, SK_ATTN = 1, SK_OPROJ = 2, SK_GATEUP = 3, SK_DOWN = 
 // chain after another; two groups keep every chain running from the fork.
 constexpr int kStageGroupsDefault = 2;
 constexpr int kStreamWGs = 1024;  // workgroups of one streaming stage launch (all its stages)
-// PDM row-block GEMV launches run beside the stage compute: a few workgroups, so that most CUs (and
+// fp32 PDM row-block GEMV launches run beside the stage compute: a few workgroups, so that most CUs (and
 // their LDS) stay with the stage launches.
 constexpr int kRowsWGsDefault = 32;
 // Sampled decoding (top-k, temperature): at most this many tokens per distribution; a sampled
@@ -133,7 +133,7 @@ struct Ctx {
   BufSet b[2];      // 0: target stream, 1: PDM stream
   unsigned long long* ktrace;  // null, or the launch trace: per slot (first start, last end) wall clock
   int stream_wgs;   // workgroups of one streaming stage launch (all its stages)
-  int rows_wgs;     // at most this many workgroups per row-block (PDM) GEMV launch (0: no cap)
+  int rows_wgs;     // at most this many workgroups per PDM projection launch (0: no cap)
   int J;            // layer slots per step (longest stage)
   Sampler sam;      // sampled decoding (sam.top_k == 0: greedy)
   int post_step;    // 1: the PDM reads the features after the step's stage compute (one stage deeper)
@@ -169,16 +169,6 @@ struct Launch {
   static void oproj(const Ctx& c, const Rows& r, void* stream);
   static void gateup(const Ctx& c, const Rows& r, void* stream);
   static void down(const Ctx& c, const Rows& r, void* stream);
-  // One decoder layer of a row block whose rows share the layer (the PDM's rows in a step, or a
-  // prefill chunk; at most max_rows rows): streaming GEMVs applying each weight pair to all rows
-  // (the down projection also captures the rows' anchor when r.anch and r.cap name one), and the
-  // rows' decode attention. Five launches; the GEMV launches take at most cap_wgs workgroups (0: as
-  // many as fit at once).
-  static void rows_layer(const Ctx& c, const Rows& r, int max_rows, int cap_wgs, void* stream);
-  // sublayer k (0 QKV, 1 attention, 2 O-proj, 3 gate/up, 4 down) of rows_layer
-  static void rows_sublayer(const Ctx& c, const Rows& r, int max_rows, int k, int cap_wgs, void* stream);
-  // PDM feature projection; prefill = 1: nrows rows of pf_anch at full depth.
-  static void pdm_fc(const Ctx& c, int prefill, int nrows, void* stream);
   // LM head + argmax partials. src: 0 = target exit row (skipped unless a == n), 1 = PDM last row,
   // 2 = prefill row `row` of pf_x, 3 = exit row and PDM row in one pass. The kernel that follows
   // (verify / reseed) reduces the partials.
@@ -193,7 +183,18 @@ struct Launch {
   // reseed that follows reads).
   static void head_sample(const Ctx& c, int src, int row, int pos, int forced_override, int auto_rb,
                           void* stream);
-  static void embed_rows(const Ctx& c, int t0, int nrows, void* stream);
+};
+// Row blocks of fp32 models (bf16 models' go through spd_prefill.h): the draft module's rows in a step and
+// the prefill's 8-row chunks.
+struct RowsF32 {
+  // One decoder layer of a row block whose rows share the layer (at most max_rows rows): streaming GEMVs
+  // applying each weight pair to all rows (the down projection also captures the rows' anchor when
+  // r.anch and r.cap name one), and the rows' decode attention. Five launches; the GEMV launches take at
+  // most cap_wgs workgroups (0: as many as fit at once).
+  static void layer(const Ctx& c, const Rows& r, int max_rows, int cap_wgs, void* stream);
+  // PDM feature projection; prefill = 1: nrows rows of pf_anch at full depth.
+  static void pdm_fc(const Ctx& c, int prefill, int nrows, void* stream);
+  static void embed(const Ctx& c, int t0, int nrows, void* stream);
 };
 void launch_ktrace_reset(const Ctx& c, int nslots, void* stream);
 // Streaming read of n16 16-byte blocks (a bandwidth probe); sink gets one float per workgroup.

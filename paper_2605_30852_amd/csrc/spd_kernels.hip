@@ -940,35 +940,6 @@ __global__ __launch_bounds__(kWG) void k_attn_rows(Ctx C, Rows R, int nrg) {
                                    k1, pos0, page0, lds);
 }
 
-// Row-block attention of bf16 caches on matrix cores: one workgroup per (key split, KV head, group of
-// 32 / G rows) serves every query of its rows (attn_split_mfma). Grid: x = key split, y = KV head,
-// z = row group; splits past the group's last key return at once.
-template <int DH>
-__global__ __launch_bounds__(kWG, 2) void k_attn_rows_mfma(Ctx C, Rows R) {
-  extern __shared__ __align__(16) float lds[];
-  const Grp gr = resolve(C, R, 0);
-  const int rpg = 32 / C.G, r0 = blockIdx.z * rpg;
-  if (!gr.active || r0 >= gr.nrows) return;
-  const int split = blockIdx.x, g = blockIdx.y, nr = min(rpg, gr.nrows - r0), pos0 = gr.pos0 + r0;
-  if (split * C.chunk >= pos0 + nr) return;
-  const BufSet& B = C.b[R.set];
-  const size_t row0 = (size_t)(gr.brow0 + r0) * C.qdim, rec0 = (size_t)r0 * C.hkv;
-  attn_split_mfma<DH>(C, (const uint16_t*)C.lay[gr.layer].kv, B.q + row0, B.ao + row0,
-                      B.part + rec0 * C.max_splits * (kAttnMaxQ * (DH + 2)), g, split, nr, pos0 + nr, LimPos{pos0},
-                      attn_mfma_page0(C, split), lds);
-}
-
-// The rows' split records into their outputs. Grid: x = KV head, y = row.
-template <int DH>
-__global__ __launch_bounds__(kWG) void k_attn_rows_merge(Ctx C, Rows R) {
-  __shared__ __align__(16) float sm[2 * kMaxSplits * kAttnMaxQ];
-  const Grp gr = resolve(C, R, 0);
-  const int r = blockIdx.y;
-  if (!gr.active || r >= gr.nrows) return;
-  const BufSet& B = C.b[R.set];
-  attn_merge_row<DH>(C, B.part, B.ao + (size_t)gr.brow0 * C.qdim, r, blockIdx.x, gr.pos0 + r + 1, sm);
-}
-
 // Launch trace reset.
 __global__ __launch_bounds__(kWG) void k_ktrace_reset(Ctx C, int nslots) {
   for (int i = blockIdx.x * kWG + threadIdx.x; i < nslots; i += gridDim.x * kWG) {
@@ -1427,21 +1398,19 @@ static void rgemv_launch(const Ctx& c, const Rows& r, int npairs, int K, int max
   // K-split (uncapped row blocks: the fp32 prefill's chunks): every chunk of every row in one pass over
   // the weights, a small LDS slice per workgroup. A capped launch (side work beside the stage compute)
   // keeps the full-width form: with few columns the split's last-arriver merges run long.
-  if constexpr (std::is_same<WT, float>::value) {
-    if (cap_wgs <= 0 && stream_lds<WT>(K) * rows > (size_t)kRowLdsBudget && K > kRowSplitK &&
-        min_cols <= kRowSplitCols) {
-      const int ns = (K + kRowSplitK - 1) / kRowSplitK;
-      const size_t shm = (size_t)rows * kRowSplitK * sizeof(float);
-      const int resident = dev_limits().cus * std::max(1, (int)((size_t)dev_limits().lds_max / (shm + 1024)));
-      const int cols = std::min(std::max(std::min(stream_grid(c, npairs, 1), std::max(1, resident / ns)), min_cols),
-                                kRowSplitCols);
-      const dim3 grid(cols, ns);
-      if (rows <= 4)
-        launch_timed((k_rgemv_ks<WT, KIND, 4>), grid, dim3(kWG), shm, S(s), c, r);
-      else
-        launch_timed((k_rgemv_ks<WT, KIND, 8>), grid, dim3(kWG), shm, S(s), c, r);
-      return;
-    }
+  if (cap_wgs <= 0 && stream_lds<WT>(K) * rows > (size_t)kRowLdsBudget && K > kRowSplitK &&
+      min_cols <= kRowSplitCols) {
+    const int ns = (K + kRowSplitK - 1) / kRowSplitK;
+    const size_t shm = (size_t)rows * kRowSplitK * sizeof(float);
+    const int resident = dev_limits().cus * std::max(1, (int)((size_t)dev_limits().lds_max / (shm + 1024)));
+    const int cols = std::min(std::max(std::min(stream_grid(c, npairs, 1), std::max(1, resident / ns)), min_cols),
+                              kRowSplitCols);
+    const dim3 grid(cols, ns);
+    if (rows <= 4)
+      launch_timed((k_rgemv_ks<WT, KIND, 4>), grid, dim3(kWG), shm, S(s), c, r);
+    else
+      launch_timed((k_rgemv_ks<WT, KIND, 8>), grid, dim3(kWG), shm, S(s), c, r);
+    return;
   }
   const int nrp = rows_per_pass<WT>(K, max_rows);
   const size_t shm = stream_lds<WT>(K) * nrp;
@@ -1458,45 +1427,26 @@ static void rgemv_launch(const Ctx& c, const Rows& r, int npairs, int K, int max
     launch_timed((k_rgemv<WT, KIND, 8>), grid, dim3(kWG), shm, S(s), c, r, nrp);
 }
 
-template <typename WT>
-void Launch<WT>::rows_layer(const Ctx& c, const Rows& r, int max_rows, int cap_wgs, void* s) {
-  for (int k = 0; k < 5; k++) rows_sublayer(c, r, max_rows, k, cap_wgs, s);
-}
-
-template <typename WT>
-void Launch<WT>::rows_sublayer(const Ctx& c, const Rows& r, int max_rows, int k, int cap_wgs, void* s) {
+void RowsF32::layer(const Ctx& c, const Rows& r, int max_rows, int cap_wgs, void* s) {
   max_rows = std::max(1, std::min(max_rows, kMaxRows));
-  if (k == 0) rgemv_launch<WT, SG_QKV>(c, r, (c.hq + 2 * c.hkv) * (c.dh / 2), c.d, max_rows, cap_wgs, s);
-  if (k == 2) rgemv_launch<WT, SG_OPROJ>(c, r, (c.d + 1) / 2, c.qdim, max_rows, cap_wgs, s);
-  if (k == 3) rgemv_launch<WT, SG_GATEUP>(c, r, c.F, c.d, max_rows, cap_wgs, s);
-  if (k == 4) rgemv_launch<WT, SG_DOWN>(c, r, (c.d + 1) / 2, c.F, max_rows, cap_wgs, s);
-  if (k != 1) return;
-  if constexpr (std::is_same<WT, uint16_t>::value) {
-    const int rpg = 32 / c.G, M = std::min(max_rows, rpg) * c.G;
-    const dim3 grid(c.max_splits, c.hkv, (max_rows + rpg - 1) / rpg), mgrid(c.hkv, max_rows);
-    if (c.dh == 128) {
-      launch_timed((k_attn_rows_mfma<128>), grid, dim3(kWG), attn_mfma_lds<128>(M), S(s), c, r);
-      if (c.max_splits > 1) launch_timed((k_attn_rows_merge<128>), mgrid, dim3(kWG), 0, S(s), c, r);
-    } else {
-      launch_timed((k_attn_rows_mfma<64>), grid, dim3(kWG), attn_mfma_lds<64>(M), S(s), c, r);
-      if (c.max_splits > 1) launch_timed((k_attn_rows_merge<64>), mgrid, dim3(kWG), 0, S(s), c, r);
-    }
+  rgemv_launch<float, SG_QKV>(c, r, (c.hq + 2 * c.hkv) * (c.dh / 2), c.d, max_rows, cap_wgs, s);
+  const int groups8 = (c.max_splits * c.hkv + 7) / 8 * 8;  // see k_attn_rows: XCD-aware order
+  const dim3 agrid(groups8 * max_rows);
+  const bool g4 = c.G <= 4;
+  if (c.dh == 128) {
+    if (g4)
+      launch_timed((k_attn_rows<float, 128, 4>), agrid, dim3(kWG), attn_split_lds<float, 128>(), S(s), c, r, max_rows);
+    else
+      launch_timed((k_attn_rows<float, 128, 8>), agrid, dim3(kWG), attn_split_lds<float, 128>(), S(s), c, r, max_rows);
   } else {
-    const int groups8 = (c.max_splits * c.hkv + 7) / 8 * 8;  // see k_attn_rows: XCD-aware order
-    const dim3 agrid(groups8 * max_rows);
-    const bool g4 = c.G <= 4;
-    if (c.dh == 128) {
-      if (g4)
-        launch_timed((k_attn_rows<WT, 128, 4>), agrid, dim3(kWG), attn_split_lds<WT, 128>(), S(s), c, r, max_rows);
-      else
-        launch_timed((k_attn_rows<WT, 128, 8>), agrid, dim3(kWG), attn_split_lds<WT, 128>(), S(s), c, r, max_rows);
-    } else {
-      if (g4)
-        launch_timed((k_attn_rows<WT, 64, 4>), agrid, dim3(kWG), attn_split_lds<WT, 64>(), S(s), c, r, max_rows);
-      else
-        launch_timed((k_attn_rows<WT, 64, 8>), agrid, dim3(kWG), attn_split_lds<WT, 64>(), S(s), c, r, max_rows);
-    }
+    if (g4)
+      launch_timed((k_attn_rows<float, 64, 4>), agrid, dim3(kWG), attn_split_lds<float, 64>(), S(s), c, r, max_rows);
+    else
+      launch_timed((k_attn_rows<float, 64, 8>), agrid, dim3(kWG), attn_split_lds<float, 64>(), S(s), c, r, max_rows);
   }
+  rgemv_launch<float, SG_OPROJ>(c, r, (c.d + 1) / 2, c.qdim, max_rows, cap_wgs, s);
+  rgemv_launch<float, SG_GATEUP>(c, r, c.F, c.d, max_rows, cap_wgs, s);
+  rgemv_launch<float, SG_DOWN>(c, r, (c.d + 1) / 2, c.F, max_rows, cap_wgs, s);
 }
 
 template <typename WT>
@@ -1522,10 +1472,9 @@ void Launch<WT>::attn(const Ctx& c, const Rows& r, void* s) {
   }
 }
 
-template <typename WT>
-void Launch<WT>::pdm_fc(const Ctx& c, int prefill, int nrows, void* s) {
+void RowsF32::pdm_fc(const Ctx& c, int prefill, int nrows, void* s) {
   const dim3 grid((c.d + 7) / 8);
-  launch_timed((k_pdm_fc<WT>), grid, dim3(kWG), gemv_lds<WT>(c.n * c.d, kMaxRows), S(s), c, prefill, nrows);
+  launch_timed((k_pdm_fc<float>), grid, dim3(kWG), gemv_lds<float>(c.n * c.d, kMaxRows), S(s), c, prefill, nrows);
 }
 
 // Workgroups of `fn` (with `lds` bytes of dynamic LDS) that the GPU holds at once.
@@ -1597,9 +1546,8 @@ void Launch<WT>::head_sample(const Ctx& c, int src, int row, int pos, int forced
                  auto_rb, lcap);
 }
 
-template <typename WT>
-void Launch<WT>::embed_rows(const Ctx& c, int t0, int nrows, void* s) {
-  launch_timed((k_embed_rows<WT>), dim3(nrows), dim3(kWG), 0, S(s), c, t0, nrows);
+void RowsF32::embed(const Ctx& c, int t0, int nrows, void* s) {
+  launch_timed((k_embed_rows<float>), dim3(nrows), dim3(kWG), 0, S(s), c, t0, nrows);
 }
 
 template struct Launch<float>;

@@ -1,5 +1,6 @@
-// Prefill of bf16 models in chunks of up to kPrefillRows prompt rows: the launchers of spd_prefill.hip
-// and the scratch they use. Internal; not part of the C ABI.
+// Row blocks of bf16 models on matrix cores, the prefill's chunks of up to kPrefillRows prompt rows and
+// the draft module's in-flight rows: the launchers of spd_prefill.hip and the scratch they use.
+// Internal; not part of the C ABI.
 #pragma once
 #include "spd_dev.h"
 
@@ -17,7 +18,7 @@ struct Planes {
   size_t stride;
 };
 
-// Scratch of the prefill (in the workspace).
+// Scratch of the prefill, and of the draft module in a step (in the workspace).
 struct PrefillBufs {
   int rows;          // row capacity, a multiple of 128
   size_t part_cap;   // floats in part
@@ -37,5 +38,10 @@ size_t prefill_part_floats(int rows, int d, int F, int qkv_cols);
 // The whole prompt: C.tok[0, len) through the target and the draft module's caches; the last row's
 // residual ends in row *last_row of B.x. Asynchronous on stream.
 void prefill_mfma(const Ctx& C, const PrefillBufs& B, const LayerDesc* layers, int len, void* stream, int* last_row);
+
+// The draft module of one step: its feature projection and layers over the in-flight rows (Eq. agg-main,
+// Eq. input-seq), the rows ending in C.pdm_x. max_rows: the SPD width; cap: at most this many workgroups
+// per projection launch (0: no cap). Asynchronous on stream; nothing depends on host state.
+void pdm_rows_mfma(const Ctx& C, const PrefillBufs& B, const LayerDesc* layers, int max_rows, int cap, void* stream);
 
 }  // namespace spd

@@ -1,4 +1,4 @@
-// Prefill of bf16 models on matrix cores.
+// Row blocks of bf16 models on matrix cores: the prompt's prefill, and the draft module's rows in a step.
 //
 // A chunk of prompt rows goes through a layer as four dense projections and one causal attention. The
 // activations stay fp32 in value: every fp32 operand x is cut into three bf16 planes by truncation,
@@ -10,6 +10,7 @@
 
 #include <algorithm>
 
+#include "spd_attn.h"
 #include "spd_devfn.h"
 #include "spd_prefill.h"
 
@@ -53,6 +54,7 @@ __device__ __forceinline__ void store_planes4(const Planes& P, size_t at, float 
 // projection before it, in split order; v becomes x. With a gain, v * gain goes to the planes of the
 // next projection and 1 / rms(v) to rs; raw: v's own planes (the draft module's stage input).
 struct NormArgs {
+  const DevState* st;    // rows: the in-flight tokens of a step (null: the grid's rows)
   float* x;
   int d, S, base;        // base: 0 x, 1 the token's embedding, 2 zero
   const float* part;     // [S][rows][d], row stride d
@@ -65,11 +67,13 @@ struct NormArgs {
   float* rs;
 };
 
+constexpr int kPartBatch = 8;                  // partial sums loaded at once
 constexpr int kNormVec = 8192 / 4 / kWG;  // float4 groups per thread at the largest d
 
 __global__ __launch_bounds__(kWG) void k_pf_norm(NormArgs A) {
   __shared__ float red[4];
   const int m = blockIdx.x, d = A.d, n4 = d >> 2;
+  if (A.st != nullptr && m >= A.st->a) return;
   float* x = A.x + (size_t)m * d;
   const uint16_t* E = A.base == 1 ? A.embed + (size_t)A.tok[m] * d : nullptr;
   float4 v[kNormVec];
@@ -85,12 +89,20 @@ __global__ __launch_bounds__(kWG) void k_pf_norm(NormArgs A) {
       const uint2 e = *reinterpret_cast<const uint2*>(E + k4 * 4);
       t = make_float4(bf_lo(e.x), bf_hi(e.x), bf_lo(e.y), bf_hi(e.y));
     }
-    for (int s = 0; s < A.S; s++) {
-      const float4 p = *reinterpret_cast<const float4*>(A.part + s * A.part_stride + (size_t)m * d + k4 * 4);
-      t.x += p.x;
-      t.y += p.y;
-      t.z += p.z;
-      t.w += p.w;
+    const float* pp = A.part + (size_t)m * d + k4 * 4;
+    for (int s0 = 0; s0 < A.S; s0 += kPartBatch) {  // a batch's loads are in flight together
+      float4 p[kPartBatch];
+#pragma unroll
+      for (int j = 0; j < kPartBatch; j++)
+        if (s0 + j < A.S) p[j] = *reinterpret_cast<const float4*>(pp + (s0 + j) * A.part_stride);
+#pragma unroll
+      for (int j = 0; j < kPartBatch; j++)
+        if (s0 + j < A.S) {
+          t.x += p[j].x;
+          t.y += p[j].y;
+          t.z += p[j].z;
+          t.w += p[j].w;
+        }
     }
     ss = fmaf(t.x, t.x, ss);
     ss = fmaf(t.y, t.y, ss);
@@ -166,11 +178,34 @@ struct GemmArgs {
   const uint16_t* zeros;
   int M, K, ldw;
   int cols;                       // plain: columns; pair kinds: pairs (two columns each)
-  int KS;                         // K range of a split, a multiple of 64
+  int KS, S;                      // K range of a split, a multiple of 64; splits
   int mt, nt;                     // tiles
   float* part;                    // null: the pair epilogue
   PairOut out;
+  const DevState* st;             // row GEMM: M is the step's in-flight tokens (null: M)
+  unsigned long long* trace;      // row GEMM: launch-trace slot (null: none)
 };
+
+// Source row of tile row rb of the weights (rows past the matrix re-read its last one; their results are
+// not stored). Pair kinds interleave the two matrices' rows, or a head's RoPE partners, by 32.
+template <int KIND>
+__device__ __forceinline__ const uint16_t* weight_row(const GemmArgs& G, int n0, int rb) {
+  if (KIND == GK_PLAIN) return G.w0 + (size_t)min(n0 + rb, G.cols - 1) * G.ldw;
+  const int which = (rb >> 5) & 1, q = min((n0 >> 1) + (rb >> 6) * 32 + (rb & 31), G.cols - 1);
+  if (KIND == GK_GATEUP) return (which ? G.w1 : G.w0) + (size_t)q * G.ldw;
+  const int half = G.out.dh >> 1, head = q / half, j = q - head * half;
+  const uint16_t* W = G.w0;
+  int hr = head;
+  if (head >= G.out.hq) {
+    hr -= G.out.hq;
+    W = G.w1;
+    if (hr >= G.out.hkv) {
+      hr -= G.out.hkv;
+      W = G.w2;
+    }
+  }
+  return W + ((size_t)hr * G.out.dh + j + which * half) * G.ldw;
+}
 
 // C = A W^T over a BM x BN tile: a workgroup of NWM x NWN waves, each WM x WN in 32 x 32 MFMA tiles.
 // The three A planes and the W rows of a K step of BK go to LDS with direct 16-byte global loads
@@ -209,45 +244,16 @@ __global__ __launch_bounds__(64 * NWM * NWN, 2) void k_pf_gemm(GemmArgs G) {
   const int mi = b % G.mt, ni = (b / G.mt) % G.nt, z = b / (G.mt * G.nt);
   const int m0 = mi * BM, n0 = ni * BN;
   const int kb = z * G.KS, ke = min(G.K, kb + G.KS);
-  const int half = G.out.dh >> 1;
 
-  // source of this thread's chunk i: row R = plane * BM + row, or a weight row (rows past the matrix
-  // re-read its last one; their results are not stored)
+  // source of this thread's chunk i: row R = plane * BM + row, or a weight row
   const uint16_t* src[CPT];
   int kc[CPT];
 #pragma unroll
   for (int i = 0; i < CPT; i++) {
     const int t = i * NTH + tid, row = t / NCH, c = (t % NCH) ^ (NCH == 4 ? (row >> 1) & 3 : row & 7);
     kc[i] = c * 8;
-    if (row < 3 * BM) {
-      src[i] = G.a.p + (row / BM) * G.a.stride + (size_t)min(m0 + row % BM, G.M - 1) * G.K + c * 8;
-    } else {
-      const int rb = row - 3 * BM;
-      const uint16_t* W = G.w0;
-      size_t n;
-      if (KIND == GK_PLAIN) {
-        n = min(n0 + rb, G.cols - 1);
-      } else {
-        const int which = (rb >> 5) & 1, q = min((n0 >> 1) + (rb >> 6) * 32 + (rb & 31), G.cols - 1);
-        if (KIND == GK_GATEUP) {
-          n = q;
-          if (which) W = G.w1;
-        } else {
-          const int head = q / half, j = q - head * half;
-          int hr = head;
-          if (head >= G.out.hq) {
-            hr -= G.out.hq;
-            W = G.w1;
-            if (hr >= G.out.hkv) {
-              hr -= G.out.hkv;
-              W = G.w2;
-            }
-          }
-          n = (size_t)hr * G.out.dh + j + which * half;
-        }
-      }
-      src[i] = W + n * G.ldw + c * 8;
-    }
+    src[i] = (row < 3 * BM ? G.a.p + (row / BM) * G.a.stride + (size_t)min(m0 + row % BM, G.M - 1) * G.K
+                           : weight_row<KIND>(G, n0, row - 3 * BM)) + c * 8;
   }
   auto issue = [&](int buf, int k) {  // inputs k .. k + BK (zeros past the split's end)
 #pragma unroll
@@ -392,22 +398,175 @@ __global__ __launch_bounds__(64 * NWM * NWN, 2) void k_pf_gemm(GemmArgs G) {
   }
 }
 
-// The pair epilogue of a K-split projection: the splits added in order. Grid: x pairs, y rows.
+// The same product for up to eight rows (the draft module's in-flight rows, a prompt's last or only
+// rows): the three planes of the eight rows are 24 of the 32 rows of ONE MFMA operand, so a weight takes
+// one MFMA and a lane ends with the three planes' sums of its rows in registers v, v + 4 and v + 8. Four
+// waves x 32 weight rows, steps of 64 inputs through kRowBufs LDS buffers; partial sums [split][8][column].
+// Workgroup b takes jobs b, b + grid, .. of the tiles x splits.
+// Bound: the weights' stream. In a step of the 4B class, beside the stage compute, the draft module's
+// gate/up (99.6 MB) takes 24 us, where a vector GEMV held to 32 workgroups so as to leave the stages
+// their LDS took 278. A cap on the workgroups (spd_set_pdm_grid) only lengthens the step: 4B n = 4
+// 36.0 ms per 24 steps without one, 36.4 at 64 workgroups; 9B n = 8 34.6 per 20 steps, 36.0 at 64.
+constexpr int kRowBufs = 3;
 template <int KIND>
-__global__ __launch_bounds__(kWG) void k_pf_pairs(PairOut O, const float* part, int S, int M, int pairs) {
+__global__ __launch_bounds__(kWG, 2) void k_pf_rows(GemmArgs G) {
+  constexpr int BN = 128, BK = 64, ROWS = 32 + BN, CPT = ROWS * 8 / kWG, BUF = ROWS * BK * 2, NS = BK / 16;
+  extern __shared__ __align__(16) char plds[];
+  const int M = G.st != nullptr ? G.st->a : G.M;
+  if (M <= 0) return;
+  if (G.trace != nullptr && blockIdx.x == 0 && threadIdx.x == 0) G.trace[0] = (unsigned long long)wall_clock64();
+  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, r = lane & 31, h = lane >> 5;
+  const int ncol = KIND == GK_PLAIN ? G.cols : 2 * G.cols, jobs = G.nt * G.S;
+  for (int job = blockIdx.x; job < jobs; job += gridDim.x) {
+    const int n0 = (job % G.nt) * BN, z = job / G.nt, kb = z * G.KS, ke = min(G.K, kb + G.KS);
+    const uint16_t* src[CPT];
+    int kc[CPT];
+#pragma unroll
+    for (int i = 0; i < CPT; i++) {
+      const int t = i * kWG + tid, row = t / 8, c = (t % 8) ^ (row & 7);
+      kc[i] = c * 8;
+      src[i] = (row < 32 ? G.a.p + min(row >> 3, 2) * G.a.stride + (size_t)min(row & 7, M - 1) * G.K
+                         : weight_row<KIND>(G, n0, row - 32)) + c * 8;
+    }
+    auto issue = [&](int buf, int k) {  // zeros past the split's end, so that every step waits for as many loads
+#pragma unroll
+      for (int i = 0; i < CPT; i++) {
+        const uint16_t* p = k + kc[i] < ke ? src[i] + k : G.zeros;
+        lbytes* const to = (lbytes*)(plds + buf * BUF + (i * kWG + w * 64) * 16);
+        if (i == 0)  // the activations' 32 rows
+          __builtin_amdgcn_global_load_lds((gbytes*)p, to, 16, 0, 0);
+        else  // weights, read once: non-temporal
+          __builtin_amdgcn_global_load_lds((gbytes*)p, to, 16, 0, 2);
+      }
+    };
+    auto frag = [&](const char* base, int row, int s) {
+      return *reinterpret_cast<const bf16x8*>(base + (row + r) * BK * 2 + (((2 * s + h) ^ (r & 7)) << 4));
+    };
+    float tot[12];
+#pragma unroll
+    for (int v = 0; v < 12; v++) tot[v] = 0.f;
+#pragma unroll
+    for (int i = 0; i < kRowBufs - 1; i++) issue(i, kb + i * BK);
+    int rd = 0, wr = kRowBufs - 1;
+    for (int k = kb; k < ke; k += BK) {
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((kRowBufs - 2) * CPT) : "memory");
+      issue(wr, k + (kRowBufs - 1) * BK);
+      wr = wr + 1 == kRowBufs ? 0 : wr + 1;
+      const char* base = plds + rd * BUF;
+      rd = rd + 1 == kRowBufs ? 0 : rd + 1;
+      f32x16 acc;
+#pragma unroll
+      for (int s = 0; s < NS; s++)
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(base, 0, s), frag(base, 32 + w * 32, s),
+                                                      s == 0 ? (f32x16)(0.f) : acc, 0, 0, 0);
+#pragma unroll
+      for (int v = 0; v < 12; v++) tot[v] += acc[v];
+    }
+    // the zero loads past the end have landed and every wave is done with the buffers
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    int col;
+    bool ok;
+    if (KIND == GK_PLAIN) {
+      col = n0 + w * 32 + r;
+      ok = col < G.cols;
+    } else {
+      const int q = (n0 >> 1) + (w >> 1) * 32 + r;
+      col = (w & 1) * G.cols + q;
+      ok = q < G.cols;
+    }
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+      const int m = 4 * h + e;
+      if (ok && m < M) G.part[((size_t)z * kMaxRows + m) * ncol + col] = (tot[8 + e] + tot[4 + e]) + tot[e];
+    }
+  }
+  if (G.trace != nullptr && threadIdx.x == 0)
+    __hip_atomic_fetch_max(G.trace + 1, (unsigned long long)wall_clock64(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The pair epilogue of a K-split projection: the splits added in order. Grid: x pairs, y rows. part:
+// [split][prows][column].
+template <int KIND>
+__global__ __launch_bounds__(kWG) void k_pf_pairs(PairOut O, const float* part, int S, int prows, int pairs,
+                                                  const DevState* st) {
   const int q = blockIdx.x * kWG + threadIdx.x, m = blockIdx.y;
+  if (st != nullptr) {
+    if (m >= st->a) return;
+    O.pos0 = st->c;
+  }
   if (q >= pairs) return;
   float s0 = 0.f, s1 = 0.f;
-  for (int s = 0; s < S; s++) {
-    const float* p = part + ((size_t)s * M + m) * 2 * pairs + q;
-    s0 += p[0];
-    s1 += p[pairs];
+  const float* pp = part + (size_t)m * 2 * pairs + q;
+  const size_t stride = (size_t)prows * 2 * pairs;
+  for (int b = 0; b < S; b += kPartBatch) {
+    float p0[kPartBatch], p1[kPartBatch];
+#pragma unroll
+    for (int j = 0; j < kPartBatch; j++)
+      if (b + j < S) {
+        p0[j] = pp[(b + j) * stride];
+        p1[j] = pp[(b + j) * stride + pairs];
+      }
+#pragma unroll
+    for (int j = 0; j < kPartBatch; j++)
+      if (b + j < S) {
+        s0 += p0[j];
+        s1 += p1[j];
+      }
   }
   const float sc = O.rs[m];
   if (KIND == GK_QKV)
     qkv_store(O, m, q, s0 * sc, s1 * sc);
   else
     act_store(O, m, q, s0 * sc, s1 * sc);
+}
+
+// --------------------------------------------------------------------------- draft module's features
+// The in-flight rows' anchors as planes [a][n * d], zeros for the anchors a row has not reached: row i at
+// depth a - 1 - i before the step (one deeper in the post-step schedule). Grid: x columns, y rows.
+__global__ __launch_bounds__(kWG) void k_pdm_feat(Ctx C, Planes out) {
+  const int i = blockIdx.y, a = C.st->a, k = (blockIdx.x * kWG + threadIdx.x) * 4, K = C.n * C.d;
+  if (i >= a || k >= K) return;
+  const int depth = a - 1 - i + C.post_step, nelig = (min(depth, C.n - 1) + 1) * C.d;
+  float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (k < nelig) v = *reinterpret_cast<const float4*>(C.anchors + (size_t)((C.st->c + i) % C.n) * K + k);
+  store_planes4(out, (size_t)i * K + k, v.x, v.y, v.z, v.w);
+}
+
+// The draft module's row attention (attn_split_mfma): one workgroup per (key split, KV head, group of
+// 32 / G rows); splits past the group's last key return at once. Outputs as planes [a][Hq*dh].
+struct PlaneOut {
+  Planes P;
+  __device__ __forceinline__ void operator()(size_t at, float a, float b) const {
+    uint32_t h[2], m[2], l[2];
+    split3(a, h[0], m[0], l[0]);
+    split3(b, h[1], m[1], l[1]);
+    *reinterpret_cast<uint32_t*>(P.p + at) = h[0] | h[1] << 16;
+    *reinterpret_cast<uint32_t*>(P.p + P.stride + at) = m[0] | m[1] << 16;
+    *reinterpret_cast<uint32_t*>(P.p + 2 * P.stride + at) = l[0] | l[1] << 16;
+  }
+};
+
+template <int DH>
+__global__ __launch_bounds__(kWG, 2) void k_pdm_attn(Ctx C, const uint16_t* kv, Planes out) {
+  extern __shared__ __align__(16) float lds[];
+  const int rpg = 32 / C.G, r0 = blockIdx.z * rpg, split = blockIdx.x;
+  const int page0 = attn_mfma_page0(C, split);
+  const int nr = min(rpg, C.st->a - r0), pos0 = C.st->c + r0;
+  if (nr <= 0 || split * C.chunk >= pos0 + nr) return;
+  const BufSet& B = C.b[1];
+  out.p += (size_t)r0 * C.qdim;
+  attn_split_mfma<DH>(C, kv, B.q + (size_t)r0 * C.qdim, PlaneOut{out},
+                      B.part + (size_t)r0 * C.hkv * C.max_splits * (kAttnMaxQ * (DH + 2)), blockIdx.y, split, nr,
+                      pos0 + nr, LimPos{pos0}, page0, lds);
+}
+
+// The rows' split records into their output planes. Grid: x = KV head, y = row.
+template <int DH>
+__global__ __launch_bounds__(kWG) void k_pdm_attn_merge(Ctx C, Planes out) {
+  __shared__ __align__(16) float sm[2 * kMaxSplits * kAttnMaxQ];
+  const int r = blockIdx.y;
+  if (r >= C.st->a) return;
+  attn_merge_row<DH>(C, C.b[1].part, PlaneOut{out}, r, blockIdx.x, C.st->c + r + 1, sm);
 }
 
 // --------------------------------------------------------------------------------- causal attention
@@ -613,7 +772,7 @@ __global__ __launch_bounds__(kWG, 2) void k_pf_attn(AttnArgs A) {
 }
 
 // ---------------------------------------------------------------------------------------- launches
-// Tile and K splits of a projection. Above 192 rows the tiles are 128 x 256, one eight-wave workgroup
+// Tile and K splits of a projection. Up to eight rows take the row GEMM (k_pf_rows). Above 192 rows the tiles are 128 x 256, one eight-wave workgroup
 // per CU; up to 192 rows 64 x 128 and up to 32 rows 32 x 128, two workgroups per CU: fewer padding rows
 // and more workgroups where the weights' stream is the bound (19456 x 2560 at 128 rows: 55 us against
 // 107 us; at 45 rows 39 us). The splits are those of the least cost, in inputs of one tile: a round of
@@ -625,14 +784,14 @@ struct GemmPlan {
 
 GemmPlan plan_gemm(int M, int cols, int K, size_t part_cap) {
   GemmPlan p;
-  p.bm = M <= 32 ? 32 : M <= 192 ? 64 : 128;
+  p.bm = M <= kMaxRows ? kMaxRows : M <= 32 ? 32 : M <= 192 ? 64 : 128;
   const int bn = p.bm == 128 ? 256 : 128, slots = p.bm == 128 ? 256 : 512;
   const long long tiles = (long long)((M + p.bm - 1) / p.bm) * ((cols + bn - 1) / bn);
   double best = 0.0;
   p.S = 1;
   for (int S = 1; S <= kPrefillMaxSplit; S++) {
     const int KS = ((K + S - 1) / S + 63) / 64 * 64;
-    if (S > 1 && ((size_t)S * M * cols > part_cap || KS < 256 || (S - 1) * KS >= K)) continue;
+    if (S > 1 && ((size_t)S * std::max(M, kMaxRows) * cols > part_cap || KS < 256 || (S - 1) * KS >= K)) continue;
     const double cost = (double)((tiles * S + slots - 1) / slots) * (KS + 288) + (S > 1 ? S * 3.3e-5 * M * cols : 0.0);
     if (S == 1 || cost < best) {
       best = cost;
@@ -653,31 +812,44 @@ void launch_gemm(GemmArgs G, int S, hipStream_t s) {
   launch_timed((k_pf_gemm<WM, WN, NWM, NWN, BK, KIND>), dim3(G.mt * G.nt * S), dim3(64 * NWM * NWN), shm, s, G);
 }
 
-// One projection; returns the number of partial sums left in B.part (0: the pair epilogue has run).
+// One projection; returns the number of partial sums left in B.part (0: the pair epilogue has run). rows:
+// G.M, or the most rows G.st can say. cap: at most this many workgroups of the row GEMM (0: no cap).
 template <int KIND>
-int gemm(const PrefillBufs& B, GemmArgs G, hipStream_t s) {
+int gemm(const PrefillBufs& B, GemmArgs G, hipStream_t s, int cap = 0) {
   const int ncol = KIND == GK_PLAIN ? G.cols : 2 * G.cols;
   const GemmPlan p = plan_gemm(G.M, ncol, G.K, B.part_cap);
   G.KS = p.KS;
+  G.S = p.S;
   G.zeros = B.zeros;
   // pairs meet in one lane only in the two-tile waves of the taller shapes
   const bool direct = KIND != GK_PLAIN && p.S == 1 && p.bm > 32;
   G.part = direct ? nullptr : B.part;
-  if (p.bm == 32)
+  int prows = G.M;
+  if (p.bm == kMaxRows) {
+    prows = kMaxRows;
+    G.nt = (ncol + 127) / 128;
+    const int jobs = G.nt * p.S;
+    launch_timed((k_pf_rows<KIND>), dim3(cap > 0 ? std::min(cap, jobs) : jobs), dim3(kWG),
+                 (size_t)kRowBufs * (32 + 128) * 64 * 2, s, G);
+  } else if (p.bm == 32) {
     launch_gemm<32, 32, 1, 4, 64, KIND>(G, p.S, s);
-  else if (p.bm == 64)
+  } else if (p.bm == 64) {
     launch_gemm<32, 64, 2, 2, 64, KIND>(G, p.S, s);
-  else
+  } else {
     launch_gemm<64, 64, 2, 4, 32, KIND>(G, p.S, s);
+  }
   if constexpr (KIND == GK_PLAIN) {
     return p.S;
   } else {
     if (!direct)
       launch_timed((k_pf_pairs<KIND>), dim3((G.cols + kWG - 1) / kWG, G.M), dim3(kWG), 0, s, G.out,
-                   (const float*)B.part, p.S, G.M, G.cols);
+                   (const float*)B.part, p.S, prows, G.cols, G.st);
     return 0;
   }
 }
+
+// Floats of one split of a plain projection of `rows` rows: see k_pf_rows and k_pf_gemm.
+size_t part_stride(int rows, int d) { return (size_t)(rows <= kMaxRows ? kMaxRows : rows) * d; }
 
 void attention(const Ctx& C, AttnArgs A, hipStream_t s) {
   const int rpw = 128 / A.G;
@@ -719,7 +891,7 @@ void prefill_mfma(const Ctx& C, const PrefillBufs& B, const LayerDesc* layers, i
       N.S = S;
       N.base = base;
       N.part = B.part;
-      N.part_stride = (size_t)rows * d;
+      N.part_stride = part_stride(rows, d);
       N.tok = C.tok + t0;
       N.embed = (const uint16_t*)C.embed;
       N.gain = gain;
@@ -819,6 +991,80 @@ void prefill_mfma(const Ctx& C, const PrefillBufs& B, const LayerDesc* layers, i
       if (i + 1 < C.ls) rest(L, B.px, 0);  // the last layer's rows are not read: its caches only
     }
   }
+}
+
+void pdm_rows_mfma(const Ctx& C, const PrefillBufs& B, const LayerDesc* layers, int max_rows, int cap, void* stream) {
+  hipStream_t s = (hipStream_t)stream;
+  const int d = C.d, K = C.n * d;
+  const Planes pa{B.pa, (size_t)kMaxRows * std::max(d, C.qdim)}, pb{B.pb, (size_t)kMaxRows * std::max(K, C.F)};
+  int S = 0;
+  auto norm = [&](int base, const float* gain) {
+    NormArgs N{};
+    N.st = C.st;
+    N.x = C.pdm_x;
+    N.d = d;
+    N.S = S;
+    N.base = base;
+    N.part = B.part;
+    N.part_stride = part_stride(max_rows, d);
+    N.gain = gain;
+    N.eps = C.eps;
+    N.out = pa;
+    N.rs = B.rs;
+    launch_timed(k_pf_norm, dim3(max_rows), dim3(kWG), 0, s, N);
+  };
+  auto args = [&](const Planes& a, int k, const void* w, int ldw, int cols) {
+    GemmArgs G{};
+    G.st = C.st;
+    G.a = a;
+    G.w0 = (const uint16_t*)w;
+    G.M = max_rows;
+    G.K = k;
+    G.ldw = ldw;
+    G.cols = cols;
+    G.out.rs = B.rs;
+    return G;
+  };
+  launch_timed(k_pdm_feat, dim3((K / 4 + kWG - 1) / kWG, max_rows), dim3(kWG), 0, s, C, pb);
+  {
+    GemmArgs G = args(pb, K, C.w_in, K, d);
+    if (C.ktrace != nullptr) G.trace = C.ktrace + 2 * (5 * C.J * C.n + KT_PDM);
+    S = gemm<GK_PLAIN>(B, G, s, cap);
+  }
+  for (int i = 0; i < C.ls; i++) {
+    const LayerDesc& L = layers[C.L + i];
+    norm(i == 0 ? 2 : 0, L.attn_norm);
+    GemmArgs Q = args(pa, d, L.wq, d, (C.hq + 2 * C.hkv) * (C.dh / 2));
+    Q.w1 = (const uint16_t*)L.wk;
+    Q.w2 = (const uint16_t*)L.wv;
+    Q.out.q = C.b[1].q;
+    Q.out.kv = (uint16_t*)L.kv;
+    Q.out.page_table = C.page_table;
+    Q.out.rope = C.rope;
+    Q.out.hq = C.hq;
+    Q.out.hkv = C.hkv;
+    Q.out.dh = C.dh;
+    Q.out.page = C.page;
+    gemm<GK_QKV>(B, Q, s, cap);
+    const int rpg = 32 / C.G, M = std::min(max_rows, rpg) * C.G;
+    const dim3 grid(C.max_splits, C.hkv, (max_rows + rpg - 1) / rpg), mgrid(C.hkv, max_rows);
+    if (C.dh == 128) {
+      launch_timed((k_pdm_attn<128>), grid, dim3(kWG), attn_mfma_lds<128>(M), s, C, (const uint16_t*)L.kv, pa);
+      if (C.max_splits > 1) launch_timed((k_pdm_attn_merge<128>), mgrid, dim3(kWG), 0, s, C, pa);
+    } else {
+      launch_timed((k_pdm_attn<64>), grid, dim3(kWG), attn_mfma_lds<64>(M), s, C, (const uint16_t*)L.kv, pa);
+      if (C.max_splits > 1) launch_timed((k_pdm_attn_merge<64>), mgrid, dim3(kWG), 0, s, C, pa);
+    }
+    S = gemm<GK_PLAIN>(B, args(pa, C.qdim, L.wo, C.qdim, d), s, cap);
+    norm(0, L.mlp_norm);
+    GemmArgs U = args(pa, d, L.wg, d, C.F);
+    U.w1 = (const uint16_t*)L.wu;
+    U.out.act = pb;
+    U.out.F = C.F;
+    gemm<GK_GATEUP>(B, U, s, cap);
+    S = gemm<GK_PLAIN>(B, args(pb, C.F, L.wd, C.F, d), s, cap);
+  }
+  norm(0, nullptr);
 }
 
 }  // namespace spd
