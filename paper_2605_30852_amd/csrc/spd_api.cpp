@@ -28,7 +28,7 @@ struct Layout {
   size_t kv, pkv, pt, rope, state, tok, forced, log, resid, anch, pdmx, pfx, pfanch, dbg, lay;
   size_t q[2], ao[2], act[2], part[2], cnt[2], hkey[2], rpart[2], rtick[2];
   size_t ktrace;
-  size_t pfpx, pfq, pfpart, pfrs, pfpa, pfpb, pfzero;  // prefill of bf16 models
+  size_t pfpx, pfpart, pfrs, pfpa, pfpb, pfzero;  // prefill of bf16 models
   int pf_rows;
   size_t su, swlog, swgmax, sqids, sqp, sqcnt, spq;  // sampled decoding
   size_t total;
@@ -126,14 +126,14 @@ Layout make_layout(const spd_config& c) {
   L.anch = take(sizeof(float) * n * n * d);
   L.pdmx = take(sizeof(float) * kMaxRows * d);
   if (c.dtype == SPD_BF16) {  // chunks on matrix cores
-    const size_t R = L.pf_rows = prefill_rows(c.max_tokens);
+    const size_t R = L.pf_rows = prefill_rows(c.max_tokens, d, c.ffn_dim, qdim, qdim + 2 * hkv * dh);
     L.pfx = take(sizeof(float) * R * d);
     L.pfpx = take(sizeof(float) * R * d);
-    L.pfq = take(sizeof(float) * R * qdim);
     L.pfpart = take(sizeof(float) * prefill_part_floats(R, d, c.ffn_dim, qdim + 2 * hkv * dh));
     L.pfrs = take(sizeof(float) * R);
     L.pfpa = take(sizeof(uint16_t) * 3 * R * std::max(d, qdim));
-    L.pfpb = take(sizeof(uint16_t) * 3 * R * std::max(d, c.ffn_dim));
+    // SwiGLU planes and raw stage inputs; the queries live between the two
+    L.pfpb = take(std::max(sizeof(uint16_t) * 3 * R * std::max(d, c.ffn_dim), sizeof(float) * R * qdim));
     L.pfzero = take(256);
   } else {  // 8-row chunks
     L.pfx = take(sizeof(float) * kMaxRows * d);
@@ -657,7 +657,7 @@ spd_status spd_init(const spd_config* cfg, const spd_weights* w, void* workspace
     P.part_cap = prefill_part_floats(P.rows, c.d_model, c.ffn_dim, C.qdim + 2 * C.kvdim);
     P.x = C.pf_x;
     P.px = (float*)(ws + lay.pfpx);
-    P.q = (float*)(ws + lay.pfq);
+    P.q = (float*)(ws + lay.pfpb);
     P.part = (float*)(ws + lay.pfpart);
     P.rs = (float*)(ws + lay.pfrs);
     P.pa = (uint16_t*)(ws + lay.pfpa);

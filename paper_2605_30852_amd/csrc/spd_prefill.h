@@ -6,9 +6,12 @@
 
 namespace spd {
 
-// Prompt rows of one chunk. Every layer's weights are read once per chunk, and 2048 rows give the
-// narrow projections (N = d) enough 128 x 128 tiles for 256 CUs; more rows would only add scratch.
-constexpr int kPrefillRows = 2048;
+// Prompt rows of one chunk: 2048 where their scratch stays within kPrefillBytes, else fewer, but at least
+// 1024 (4B class: 1024 rows, 156 MB). A layer's weights are read once per chunk, which at 1024 rows is far
+// below the matrix cores' time; narrow models need the rows to fill 256 CUs (1024 wide, 6000 tokens: 36.3 ms
+// at 2048 rows, 44.7 ms at 1024).
+constexpr int kPrefillRows = 2048, kPrefillMinRows = 1024;
+constexpr size_t kPrefillBytes = (size_t)160 << 20;
 constexpr int kPrefillMaxSplit = 16;  // K splits of one projection
 
 // An fp32 activation matrix [rows][K] as three bf16 planes whose sum is the fp32 value exactly:
@@ -24,7 +27,7 @@ struct PrefillBufs {
   size_t part_cap;   // floats in part
   float* x;          // [rows][d] residual rows of the target
   float* px;         // [rows][d] residual rows of the draft module
-  float* q;          // [rows][Hq*dh] rotated queries
+  float* q;          // [rows][Hq*dh] rotated queries, in pb's memory: read by the attention, before gate/up writes pb
   float* part;       // K-split partial sums, [split][row][column]
   float* rs;         // [rows] 1 / rms of the normalised rows
   uint16_t* pa;      // planes of [rows][max(d, Hq*dh)]: normalised rows, attention outputs
@@ -32,7 +35,7 @@ struct PrefillBufs {
   uint16_t* zeros;   // 256 bytes of zeros
 };
 
-int prefill_rows(int max_tokens);
+int prefill_rows(int max_tokens, int d, int F, int qdim, int qkv_cols);
 size_t prefill_part_floats(int rows, int d, int F, int qkv_cols);
 
 // The whole prompt: C.tok[0, len) through the target and the draft module's caches; the last row's

@@ -863,7 +863,15 @@ void attention(const Ctx& C, AttnArgs A, hipStream_t s) {
 
 }  // namespace
 
-int prefill_rows(int max_tokens) { return std::min(kPrefillRows, (max_tokens + 127) / 128 * 128); }
+int prefill_rows(int max_tokens, int d, int F, int qdim, int qkv_cols) {
+  auto bytes = [&](size_t rows) {
+    return 4 * (2 * rows * d + prefill_part_floats((int)rows, d, F, qkv_cols) + rows) + 6 * rows * std::max(d, qdim) +
+           std::max(6 * rows * std::max(d, F), 4 * rows * qdim);
+  };
+  int rows = kPrefillRows;
+  while (rows > kPrefillMinRows && bytes(rows) > kPrefillBytes) rows -= 128;
+  return std::min(rows, (max_tokens + 127) / 128 * 128);
+}
 
 // Partial sums: four splits of the narrow projections and two of QKV over a full chunk, and four of the
 // wide ones over a chunk of 128 rows (longer chunks have tiles enough without splitting those).
@@ -875,7 +883,7 @@ size_t prefill_part_floats(int rows, int d, int F, int qkv_cols) {
 void prefill_mfma(const Ctx& C, const PrefillBufs& B, const LayerDesc* layers, int len, void* stream, int* last_row) {
   hipStream_t s = (hipStream_t)stream;
   const int d = C.d, qkv_pairs = (C.hq + 2 * C.hkv) * (C.dh / 2);
-  const int nch = (len + kPrefillRows - 1) / kPrefillRows;
+  const int nch = (len + B.rows - 1) / B.rows;
   const int step = ((len + nch - 1) / nch + 127) / 128 * 128;  // equal chunks
   const size_t pa_w = std::max(d, C.qdim), pb_w = std::max(d, C.F);
   const Planes pa{B.pa, (size_t)B.rows * pa_w}, pb{B.pb, (size_t)B.rows * pb_w};
