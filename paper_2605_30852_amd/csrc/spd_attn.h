@@ -476,6 +476,36 @@ __device__ __forceinline__ int attn_mfma_page0(const Ctx& C, int split) {
   return C.page_table[min(key / C.page, C.max_pages - 1)];
 }
 
+// Query q (one head, fp32) over the keys [k0, k1) in plain fp32, for dims 2 dp and 2 dp + 1: what a split
+// with a query, key or value that is not finite needs. There a plane's 0 * inf, or a value past a shorter
+// row's last key, makes the matrix form NaN where the products themselves are not.
+template <int DH>
+__device__ __forceinline__ void attn_pair_serial(const Ctx& C, const uint16_t* kvb, const float* q, int g, int dp, int k0,
+                                                 int k1, float& M, float& L, float& a0, float& a1) {
+  auto row = [&](int key) {
+    return kvb + (size_t)C.page_table[key / C.page] * 2 * C.hkv * C.page * DH + ((size_t)g * C.page + key % C.page) * DH;
+  };
+  auto score = [&](const uint16_t* k) {
+    float s = 0.f;
+#pragma unroll 1
+    for (int d = 0; d < DH; d++) s = fmaf(q[d] * C.scale, __uint_as_float((uint32_t)k[d] << 16), s);
+    return s;
+  };
+  M = -INFINITY;
+#pragma unroll 1
+  for (int key = k0; key < k1; key++) M = fmaxf(M, score(row(key)));
+  L = a0 = a1 = 0.f;
+#pragma unroll 1
+  for (int key = k0; key < k1; key++) {
+    const uint16_t* k = row(key);
+    const uint32_t v = *reinterpret_cast<const uint32_t*>(k + (size_t)C.hkv * C.page * DH + 2 * dp);
+    const float s = score(k), p = s == -INFINITY ? 0.f : expf(s - M);
+    L += p;
+    a0 = fmaf(p, __uint_as_float(v << 16), a0);
+    a1 = fmaf(p, __uint_as_float(v & 0xffff0000u), a1);
+  }
+}
+
 // kvb: the layer's bf16 cache; q, out: query and output rows (row r at r * qdim, head g's G heads
 // contiguous); part: the split records of (row r, KV head g) at index r * hkv + g;
 // page0: attn_mfma_page0, requested by the caller; kend: the longest row's keys, [0, kend).
@@ -486,7 +516,7 @@ __device__ void attn_split_mfma(const Ctx& C, const uint16_t* kvb, const float* 
   constexpr int MAXQ = kAttnMaxQ, RS = MAXQ * (DH + 2), NWV = kWG / 64, VROW = DH * 2 + 16;
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
   const int col = lane & 31, hf = lane >> 5;
-  const int G = C.G, M = nrows * G;
+  const int G = C.G, lg = __builtin_ctz(G), M = nrows * G;  // G is a power of two
   const int k0 = split * C.chunk, k1 = min(kend, k0 + C.chunk);
   char* const lbase = reinterpret_cast<char*>(lds);
   char* const qpl = lbase;                                                  // [3][M][DH] bf16, chunks permuted
@@ -514,7 +544,7 @@ __device__ void attn_split_mfma(const Ctx& C, const uint16_t* kvb, const float* 
 
   // query planes: thread e takes eight dims of a query
   for (int e = tid; e < M * (DH / 8); e += kWG) {
-    const int j = e / (DH / 8), c = e % (DH / 8), r = j / G, h = j % G;
+    const int j = e / (DH / 8), c = e % (DH / 8), r = j >> lg, h = j & (G - 1);
     const float* qp = q + (size_t)r * C.qdim + (size_t)(g * G + h) * DH + c * 8;
     const float4 a = *reinterpret_cast<const float4*>(qp), b = *reinterpret_cast<const float4*>(qp + 4);
     const float f[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
@@ -541,10 +571,10 @@ __device__ void attn_split_mfma(const Ctx& C, const uint16_t* kvb, const float* 
       *reinterpret_cast<uint4*>(qpl + ((size_t)p * M + j) * DH * 2 + ((c ^ (j & 7)) << 4)) =
           make_uint4(pl[p][0], pl[p][1], pl[p][2], pl[p][3]);
   }
-  // this lane's query: column col; columns past M repeat one, and are not used
+  // this lane's query: column col; columns past M repeat the last one, and are not used
   const bool qon = col < M;
-  const int qc = qon ? col : col % M;
-  const int qlim = lim(qc / G);
+  const int qc = min(col, M - 1);
+  const int qlim = lim(qc >> lg);
   __syncthreads();  // queries staged
 
   float m_run = -INFINITY, l_run = 0.f;
@@ -661,40 +691,68 @@ __device__ void attn_split_mfma(const Ctx& C, const uint16_t* kvb, const float* 
   }
   __syncthreads();
 
-  // combine the waves in wave order per (query, dim pair); write a one-split row's output, else the
-  // row's split record. A query of a row that has keys in this split has a valid key in wave 0's
-  // first tile (key k0), so M is finite.
+  // Combine the waves in wave order per (query, four dims); write a one-split row's output, else the row's
+  // split record. A query of a row that has keys in this split has a valid key in wave 0's first tile (key
+  // k0), so its maximum is finite. Lane l works out the waves' factors of query l % 32 once and hands them
+  // over by shuffles: 32 queries of 128 dims with the factors per (query, dim pair), and divisions by G and
+  // the chunk, took 14.9 us per launch at 8 rows of 200 keys.
   const float* mlb = reinterpret_cast<const float*>(lbase + main_bytes);
-  for (int e = tid; e < M * (DH / 2); e += kWG) {
-    const int j = e / (DH / 2), dp = e % (DH / 2);
-    const int r = j / G, h = j % G;
-    if (k0 > lim(r)) continue;  // no key of this split for the row
-    float Mx = -INFINITY;
+  float fw[NWV], Mq = -INFINITY, Lq = 0.f;
 #pragma unroll
-    for (int wv = 0; wv < NWV; wv++) Mx = fmaxf(Mx, mlb[wv * 64 + j]);
-    float L = 0.f, a0 = 0.f, a1 = 0.f;
+  for (int wv = 0; wv < NWV; wv++) Mq = fmaxf(Mq, mlb[wv * 64 + col]);
+#pragma unroll
+  for (int wv = 0; wv < NWV; wv++) {
+    const float lw = mlb[wv * 64 + 32 + col];
+    fw[wv] = lw != 0.f ? expf(mlb[wv * 64 + col] - Mq) : 0.f;  // 0: the wave had no key of this row
+    Lq = fmaf(lw, fw[wv], Lq);
+  }
+  constexpr int TPQ = DH / 4, QPI = kWG / TPQ;  // threads per query, queries at once
+  const int d4 = tid % TPQ;
+  for (int jb = 0; jb < M; jb += QPI) {
+    const int j = jb + tid / TPQ, r = j >> lg, h = j & (G - 1);
+    float f[NWV];
+#pragma unroll
+    for (int wv = 0; wv < NWV; wv++) f[wv] = __shfl(fw[wv], j & 31, 64);
+    const float Mx = __shfl(Mq, j & 31, 64), L = __shfl(Lq, j & 31, 64);
+    if (j >= M || k0 > lim(r)) continue;  // no key of this split for the row
+    float a[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int wv = 0; wv < NWV; wv++) {
-      const float mw = mlb[wv * 64 + j];
-      if (mw != -INFINITY) {
-        const float f = expf(mw - Mx);
-        L = fmaf(mlb[wv * 64 + 32 + j], f, L);
-        const float2 ov = *reinterpret_cast<const float2*>(reinterpret_cast<const float*>(lbase) +
-                                                           ((size_t)wv * M + j) * DH + 2 * dp);
-        a0 = fmaf(ov.x, f, a0);
-        a1 = fmaf(ov.y, f, a1);
+      const float4 ov =
+          *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(lbase) + ((size_t)wv * M + j) * DH + 4 * d4);
+      a[0] = fmaf(ov.x, f[wv], a[0]);
+      a[1] = fmaf(ov.y, f[wv], a[1]);
+      a[2] = fmaf(ov.z, f[wv], a[2]);
+      a[3] = fmaf(ov.w, f[wv], a[3]);
+    }
+    float Mr = Mx, Lr = L;
+    if (L != L || a[0] != a[0] || a[1] != a[1] || a[2] != a[2] || a[3] != a[3]) {
+#pragma unroll
+      for (int i = 0; i < 4; i += 2) {
+        float Ms, Ls;
+        attn_pair_serial<DH>(C, kvb, q + (size_t)r * C.qdim + (size_t)(g * G + h) * DH, g, 2 * d4 + i / 2, k0,
+                             min(k1, lim(r) + 1), Ms, Ls, a[i], a[i + 1]);
+        if (L == L) {  // the scores were sound: the record's maximum and sum are those of the other dims
+          const float t2 = expf(Ms - Mx);
+          a[i] *= t2;
+          a[i + 1] *= t2;
+        } else {
+          Mr = Ms;
+          Lr = Ls;
+        }
       }
     }
-    const int nsplit = (lim(r) + C.chunk) / C.chunk;
-    if (nsplit == 1) {
-      const float inv = 1.0f / L;
-      out((size_t)r * C.qdim + (size_t)(g * G + h) * DH + 2 * dp, a0 * inv, a1 * inv);
+    if (lim(r) < C.chunk) {  // one split
+      const float inv = 1.0f / Lr;
+      const size_t at = (size_t)r * C.qdim + (size_t)(g * G + h) * DH + 4 * d4;
+      out(at, a[0] * inv, a[1] * inv);
+      out(at + 2, a[2] * inv, a[3] * inv);
     } else {
       float* rec = part + ((size_t)(r * C.hkv + g) * C.max_splits + split) * RS;
-      *reinterpret_cast<float2*>(rec + h * DH + 2 * dp) = make_float2(a0, a1);
-      if (dp == 0) {
-        rec[MAXQ * DH + h] = Mx;
-        rec[MAXQ * DH + MAXQ + h] = L;
+      *reinterpret_cast<float4*>(rec + h * DH + 4 * d4) = make_float4(a[0], a[1], a[2], a[3]);
+      if (d4 == 0) {
+        rec[MAXQ * DH + h] = Mr;
+        rec[MAXQ * DH + MAXQ + h] = Lr;
       }
     }
   }

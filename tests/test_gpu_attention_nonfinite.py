@@ -1,0 +1,62 @@
+"""Infinities and NaN in the paged cache of a ragged decode attention (bf16 caches on matrix cores, whose
+queries and probabilities are sums of bf16 planes): a row sees those of its own keys only, and sees them
+as plain arithmetic does. An infinite value makes its dim infinite, an infinite key gives its query NaN or,
+at minus infinity, weight zero, a NaN key spoils the rows that attend it, and nothing past a row's last key
+reaches the row. Against numpy in 64 bits; finite results to relative 1e-4 of the row, as the finite cases
+of the same call."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+def _reference(q, k, v):
+    """One query over its keys, in 64 bits."""
+    with np.errstate(all="ignore"):
+        s = k @ q / np.sqrt(len(q))
+        p = np.exp(s - s.max())
+        return (p[:, None] * v).sum(0) / p.sum()
+
+
+@pytest.mark.parametrize("keys,chunk", [(40, 64), (130, 64), (163, 48)])
+@pytest.mark.parametrize("hq,hkv,dh", [(8, 2, 128), (8, 1, 64), (2, 2, 64)])
+def test_rows_see_their_own_nonfinite_keys(hq, hkv, dh, keys, chunk):
+    from paper_2605_30852_amd import binding as B
+    rows, G, inf = 4, hq // hkv, float("inf")
+    rng = np.random.default_rng(keys + dh)
+    lens = np.array([keys - i for i in range(rows)], dtype=np.int32)
+    pages = (keys + 15) // 16 + 1
+    bf = lambda a: torch.from_numpy(a.astype(np.float32)).bfloat16()  # noqa: E731
+    base = bf(rng.standard_normal((2, pages * 16, hkv, dh)))
+    q = rng.standard_normal((rows, hq, dh)).astype(np.float32)
+    table = rng.permutation(pages).astype(np.int32)
+    marks = {"value of the longest row's last key": [(1, keys - 1, 0, 3, inf)],
+             "value of every row": [(1, 7, hkv - 1, 5, -inf)],
+             "key of every row": [(0, 9, 0, 0, inf)],
+             "NaN key of two rows": [(0, keys - 2, 0, 1, float("nan"))],
+             "past every row": [(0, keys, 0, 2, float("nan")), (1, keys, 0, 2, inf)]}
+    for what, at in marks.items():
+        kv = base.clone()
+        for part, key, head, dim, x in at:
+            kv[part, key, head, dim] = x
+        pool = torch.empty(pages, 2, hkv, 16, dh, dtype=torch.bfloat16)
+        pool[torch.from_numpy(table).long()] = kv.view(2, pages, 16, hkv, dh).permute(1, 0, 3, 2, 4)
+        pool_d, q_d, table_d = pool.cuda(), torch.from_numpy(q).cuda(), torch.from_numpy(table).cuda()
+        out = torch.zeros(rows, hq, dh, device="cuda")
+        nb = B.decode_attention_workspace_bytes(rows, hkv, dh, lens, chunk)
+        ws = torch.empty(nb + 256, dtype=torch.uint8, device="cuda")
+        print(f"[{what}: {hq}/{hkv}x{dh} keys {keys} chunk {chunk}]", flush=True)
+        B.spd_decode_attention(q_d.data_ptr(), pool_d.data_ptr(), table_d.data_ptr(), pages, lens, hq, hkv, dh,
+                               B.SPD_BF16, chunk, out.data_ptr(), (ws.data_ptr() + 255) // 256 * 256, nb,
+                               torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        got, x = out.cpu().numpy(), kv.double().numpy()
+        for i in range(rows):
+            for h in range(hq):
+                n = int(lens[i])
+                want = _reference(q[i, h].astype(np.float64), x[0, :n, h // G], x[1, :n, h // G])
+                fin = np.isfinite(want)
+                assert np.array_equal(got[i, h][~fin], want[~fin], equal_nan=True), (what, i, h)
+                err = np.linalg.norm((got[i, h] - want)[fin])
+                assert err <= 1e-4 * max(np.linalg.norm(want[fin]), 1e-30), (what, i, h, err)
