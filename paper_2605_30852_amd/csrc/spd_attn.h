@@ -476,34 +476,93 @@ __device__ __forceinline__ int attn_mfma_page0(const Ctx& C, int split) {
   return C.page_table[min(key / C.page, C.max_pages - 1)];
 }
 
-// Query q (one head, fp32) over the keys [k0, k1) in plain fp32, for dims 2 dp and 2 dp + 1: what a split
-// with a query, key or value that is not finite needs. There a plane's 0 * inf, or a value past a shorter
-// row's last key, makes the matrix form NaN where the products themselves are not.
+// Query q (one head, fp32) over the keys [k0, k1) of KV head g in plain fp32, by the whole workgroup: what a
+// query, key or value that is not finite needs. There a plane's 0 * inf, or a value past a shorter row's last
+// key, makes the matrix form NaN where the products themselves are not. M, L and a (dims 4 d4 .. + 3 of thread
+// d4 = tid % (DH / 4)) are the split's maximum, sum and output; true in the threads that hold them. A score
+// that is NaN or +inf makes every dim NaN, which the first pass finds: the values are then not read.
+// The scores are computed twice rather than kept, 256 keys at a time: time grows with the keys, 128 FMAs for
+// each 256 of them and pass, and memory does not. lds: kWG * 6 floats.
 template <int DH>
-__device__ __forceinline__ void attn_pair_serial(const Ctx& C, const uint16_t* kvb, const float* q, int g, int dp, int k0,
-                                                 int k1, float& M, float& L, float& a0, float& a1) {
+__device__ __forceinline__ bool attn_query_plain(const uint16_t* kvb, const int* page_table, int hkv, int g,
+                                                 const float* q, float scale, int k0, int k1, float* lds, float& M,
+                                                 float& L, float (&a)[4]) {
+  constexpr int PAGE = 16, TPQ = DH / 4, NG = kWG / TPQ;  // threads per key's value row, keys at once
+  const int tid = threadIdx.x, d4 = tid % TPQ, grp = tid / TPQ;
+  float* sp = lds;        // [kWG] probabilities
+  float* sr = lds + kWG;  // [NG][TPQ][5] sums of the key groups
   auto row = [&](int key) {
-    return kvb + (size_t)C.page_table[key / C.page] * 2 * C.hkv * C.page * DH + ((size_t)g * C.page + key % C.page) * DH;
+    return kvb + ((size_t)page_table[key / PAGE] * 2 * hkv + g) * PAGE * DH + (key % PAGE) * DH;
   };
-  auto score = [&](const uint16_t* k) {
+  auto score = [&](int key) {
+    const uint4* k = reinterpret_cast<const uint4*>(row(key));
     float s = 0.f;
-#pragma unroll 1
-    for (int d = 0; d < DH; d++) s = fmaf(q[d] * C.scale, __uint_as_float((uint32_t)k[d] << 16), s);
+#pragma unroll 4
+    for (int c = 0; c < DH / 8; c++) {
+      float f[8];
+      unpack16<uint16_t>(k[c], f);
+#pragma unroll
+      for (int e = 0; e < 8; e++) s = fmaf(q[c * 8 + e] * scale, f[e], s);
+    }
     return s;
   };
-  M = -INFINITY;
-#pragma unroll 1
-  for (int key = k0; key < k1; key++) M = fmaxf(M, score(row(key)));
-  L = a0 = a1 = 0.f;
-#pragma unroll 1
-  for (int key = k0; key < k1; key++) {
-    const uint16_t* k = row(key);
-    const uint32_t v = *reinterpret_cast<const uint32_t*>(k + (size_t)C.hkv * C.page * DH + 2 * dp);
-    const float s = score(k), p = s == -INFINITY ? 0.f : expf(s - M);
-    L += p;
-    a0 = fmaf(p, __uint_as_float(v << 16), a0);
-    a1 = fmaf(p, __uint_as_float(v & 0xffff0000u), a1);
+  float m = -INFINITY;
+  bool sound = true;
+  for (int key = k0 + tid; key < k1; key += kWG) {
+    const float s = score(key);
+    m = fmaxf(m, s);
+    sound = sound && s < INFINITY;
   }
+#pragma unroll
+  for (int i = 1; i < 64; i <<= 1) m = fmaxf(m, __shfl_xor(m, i, 64));
+  const bool wave_sound = __all(sound);
+  __syncthreads();  // the area's earlier readers are done
+  if ((tid & 63) == 0) {
+    sp[tid >> 6] = m;
+    sp[4 + (tid >> 6)] = wave_sound ? 0.f : 1.f;
+  }
+  __syncthreads();
+  M = fmaxf(fmaxf(sp[0], sp[1]), fmaxf(sp[2], sp[3]));
+  const bool all_sound = sp[4] + sp[5] + sp[6] + sp[7] == 0.f;
+  __syncthreads();
+  if (!all_sound) {  // the same in every thread
+    L = a[0] = a[1] = a[2] = a[3] = NAN;
+    return grp == 0;
+  }
+  L = a[0] = a[1] = a[2] = a[3] = 0.f;
+  for (int base = k0; base < k1; base += kWG) {
+    float p = 0.f;
+    if (base + tid < k1) {
+      const float s = score(base + tid);
+      p = s == -INFINITY ? 0.f : expf(s - M);
+    }
+    sp[tid] = p;
+    __syncthreads();
+    const int n = min(kWG, k1 - base);
+    for (int i = grp; i < n; i += NG) {
+      const uint2 v = *reinterpret_cast<const uint2*>(row(base + i) + (size_t)hkv * PAGE * DH + 4 * d4);
+      const float pk = sp[i];
+      L += pk;
+      a[0] = fmaf(pk, bf_lo(v.x), a[0]);
+      a[1] = fmaf(pk, bf_hi(v.x), a[1]);
+      a[2] = fmaf(pk, bf_lo(v.y), a[2]);
+      a[3] = fmaf(pk, bf_hi(v.y), a[3]);
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int i = 0; i < 4; i++) sr[tid * 5 + i] = a[i];
+  sr[tid * 5 + 4] = L;
+  __syncthreads();
+  if (grp != 0) return false;
+#pragma unroll 1
+  for (int i = 1; i < NG; i++) {
+    const float* o = sr + (i * TPQ + d4) * 5;
+#pragma unroll
+    for (int k = 0; k < 4; k++) a[k] += o[k];
+    L += o[4];
+  }
+  return true;
 }
 
 // kvb: the layer's bf16 cache; q, out: query and output rows (row r at r * qdim, head g's G heads
@@ -518,6 +577,8 @@ __device__ void attn_split_mfma(const Ctx& C, const uint16_t* kvb, const float* 
   const int col = lane & 31, hf = lane >> 5;
   const int G = C.G, lg = __builtin_ctz(G), M = nrows * G;  // G is a power of two
   const int k0 = split * C.chunk, k1 = min(kend, k0 + C.chunk);
+  __shared__ uint32_t s_bad;  // queries whose result here is not a number
+  if (tid == 0) s_bad = 0u;
   char* const lbase = reinterpret_cast<char*>(lds);
   char* const qpl = lbase;                                                  // [3][M][DH] bf16, chunks permuted
   char* const vt = lbase + (size_t)3 * M * DH * 2 + (size_t)w * 32 * VROW;  // this wave's V tile
@@ -708,6 +769,21 @@ __device__ void attn_split_mfma(const Ctx& C, const uint16_t* kvb, const float* 
   }
   constexpr int TPQ = DH / 4, QPI = kWG / TPQ;  // threads per query, queries at once
   const int d4 = tid % TPQ;
+  auto put = [&](int r, int h, const float (&a)[4], float Mr, float Lr) {
+    if (lim(r) < C.chunk) {  // one split
+      const float inv = 1.0f / Lr;
+      const size_t at = (size_t)r * C.qdim + (size_t)(g * G + h) * DH + 4 * d4;
+      out(at, a[0] * inv, a[1] * inv);
+      out(at + 2, a[2] * inv, a[3] * inv);
+    } else {
+      float* rec = part + ((size_t)(r * C.hkv + g) * C.max_splits + split) * RS;
+      *reinterpret_cast<float4*>(rec + h * DH + 4 * d4) = make_float4(a[0], a[1], a[2], a[3]);
+      if (d4 == 0) {
+        rec[MAXQ * DH + h] = Mr;
+        rec[MAXQ * DH + MAXQ + h] = Lr;
+      }
+    }
+  };
   for (int jb = 0; jb < M; jb += QPI) {
     const int j = jb + tid / TPQ, r = j >> lg, h = j & (G - 1);
     float f[NWV];
@@ -725,36 +801,19 @@ __device__ void attn_split_mfma(const Ctx& C, const uint16_t* kvb, const float* 
       a[2] = fmaf(ov.z, f[wv], a[2]);
       a[3] = fmaf(ov.w, f[wv], a[3]);
     }
-    float Mr = Mx, Lr = L;
-    if (L != L || a[0] != a[0] || a[1] != a[1] || a[2] != a[2] || a[3] != a[3]) {
-#pragma unroll
-      for (int i = 0; i < 4; i += 2) {
-        float Ms, Ls;
-        attn_pair_serial<DH>(C, kvb, q + (size_t)r * C.qdim + (size_t)(g * G + h) * DH, g, 2 * d4 + i / 2, k0,
-                             min(k1, lim(r) + 1), Ms, Ls, a[i], a[i + 1]);
-        if (L == L) {  // the scores were sound: the record's maximum and sum are those of the other dims
-          const float t2 = expf(Ms - Mx);
-          a[i] *= t2;
-          a[i + 1] *= t2;
-        } else {
-          Mr = Ms;
-          Lr = Ls;
-        }
-      }
-    }
-    if (lim(r) < C.chunk) {  // one split
-      const float inv = 1.0f / Lr;
-      const size_t at = (size_t)r * C.qdim + (size_t)(g * G + h) * DH + 4 * d4;
-      out(at, a[0] * inv, a[1] * inv);
-      out(at + 2, a[2] * inv, a[3] * inv);
-    } else {
-      float* rec = part + ((size_t)(r * C.hkv + g) * C.max_splits + split) * RS;
-      *reinterpret_cast<float4*>(rec + h * DH + 4 * d4) = make_float4(a[0], a[1], a[2], a[3]);
-      if (d4 == 0) {
-        rec[MAXQ * DH + h] = Mr;
-        rec[MAXQ * DH + MAXQ + h] = Lr;
-      }
-    }
+    if (L != L || a[0] != a[0] || a[1] != a[1] || a[2] != a[2] || a[3] != a[3])
+      atomicOr(&s_bad, 1u << j);
+    else
+      put(r, h, a, Mx, L);
+  }
+  __syncthreads();
+  // Queries with a NaN, one after the other in plain fp32.
+  for (uint32_t bad = __builtin_amdgcn_readfirstlane(s_bad); bad != 0u; bad &= bad - 1u) {
+    const int j = __builtin_ctz(bad), r = j >> lg, h = j & (G - 1);
+    float a[4], Mr, Lr;
+    if (attn_query_plain<DH>(kvb, C.page_table, C.hkv, g, q + (size_t)r * C.qdim + (size_t)(g * G + h) * DH, C.scale, k0,
+                             min(k1, lim(r) + 1), lds, Mr, Lr, a))
+      put(r, h, a, Mr, Lr);
   }
 }
 

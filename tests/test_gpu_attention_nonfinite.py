@@ -60,3 +60,64 @@ def test_rows_see_their_own_nonfinite_keys(hq, hkv, dh, keys, chunk):
                 assert np.array_equal(got[i, h][~fin], want[~fin], equal_nan=True), (what, i, h)
                 err = np.linalg.norm((got[i, h] - want)[fin])
                 assert err <= 1e-4 * max(np.linalg.norm(want[fin]), 1e-30), (what, i, h, err)
+
+
+def _call_us(B, args, n=5):
+    """Best time of n calls, in microseconds."""
+    best = float("inf")
+    for _ in range(n):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        B.spd_decode_attention(*args, torch.cuda.current_stream().cuda_stream)
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b) * 1e3)
+    return best
+
+
+@pytest.mark.parametrize("what", ["NaN query", "NaN key", "infinite value", "key at minus infinity"])
+def test_long_split_with_nonfinite_stays_bounded(what):
+    """One split of 8192 keys whose every query needs the plain form: right, and within 100 times the finite
+    call. 16 queries in turn, each two passes of 32 keys a thread, are some 130000 dependent steps; a form in
+    which every thread walks all keys twice for each of its dim pairs needs 4.2 million a query."""
+    from paper_2605_30852_amd import binding as B
+    rows, hq, hkv, dh, keys = 4, 4, 1, 128, 8192
+    rng = np.random.default_rng(11)
+    lens = np.array([keys - i for i in range(rows)], dtype=np.int32)
+    pages = keys // 16
+    kv = torch.from_numpy(rng.standard_normal((pages, 2, hkv, 16, dh)).astype(np.float32)).bfloat16()
+    q = torch.from_numpy(rng.standard_normal((rows, hq, dh)).astype(np.float32))
+    table = torch.arange(pages, dtype=torch.int32).cuda()
+    nb = B.decode_attention_workspace_bytes(rows, hkv, dh, lens, keys)
+    ws = torch.empty(nb + 256, dtype=torch.uint8, device="cuda")
+    out = torch.zeros(rows, hq, dh, device="cuda")
+
+    def args(pool, qd):
+        return (qd.data_ptr(), pool.data_ptr(), table.data_ptr(), pages, lens, hq, hkv, dh, B.SPD_BF16, keys,
+                out.data_ptr(), (ws.data_ptr() + 255) // 256 * 256, nb)
+    pool, qd = kv.cuda(), q.cuda()
+    print(f"[{what}: finite]", flush=True)
+    finite = _call_us(B, args(pool, qd))
+    if what == "NaN query":
+        q[:, :, 5] = float("nan")
+    elif what == "NaN key":
+        kv[3, 0, 0, 2, 7] = float("nan")
+    elif what == "infinite value":
+        kv[3, 1, 0, 2, 7] = float("inf")
+    else:
+        q[:, :, 7] = q[:, :, 7].abs() + 0.1
+        kv[3, 0, 0, 2, 7] = -float("inf")
+    pool, qd = kv.cuda(), q.cuda()
+    print(f"[{what}]", flush=True)
+    took = _call_us(B, args(pool, qd))
+    got, x = out.cpu().numpy(), kv.double().numpy()
+    k, v = (x[:, p].transpose(0, 2, 1, 3).reshape(-1, hkv, dh) for p in (0, 1))
+    for i in range(rows):
+        for h in range(hq):
+            n = int(lens[i])
+            want = _reference(q[i, h].double().numpy(), k[:n, 0], v[:n, 0])
+            fin = np.isfinite(want)
+            assert np.array_equal(got[i, h][~fin], want[~fin], equal_nan=True), (i, h)
+            assert np.linalg.norm(got[i, h][fin] - want[fin]) <= 1e-4 * max(np.linalg.norm(want[fin]), 1e-30), (i, h)
+    print(f"  finite {finite:.1f} us, {what} {took:.1f} us", flush=True)
+    assert took <= 100 * finite, (finite, took)
