@@ -579,6 +579,9 @@ __global__ __launch_bounds__(kWG) void k_pdm_attn_merge(Ctx C, Planes out) {
 //   * O^T += V^T P^T with p cut into planes in registers: the eight keys that half h of k step s needs
 //     are the ones the lane already holds, if V^T keeps its key quads in the order 0, 2, 1, 3.
 // K goes to LDS with direct loads, V through registers, where 4 x 8 blocks are transposed.
+// A workgroup's rows share its key tiles, so 0 * v of a value past a row's own position, or 0 * k of a query
+// plane, makes NaN of a row whose own keys and values do not: a query that ends as NaN is computed again over
+// its own keys by plain FMAs (attn_query_plain).
 // Bound: MFMA (48 per 32 keys) beside the softmax's vector work. A layer of the 4B class takes 34 us at
 // 384 rows and 105 us at 1501; the wide model's 2048-row chunks at 6000 tokens 225 us (46, 147 and 343
 // with the page of each tile read where it is used, behind the keys in flight).
@@ -588,7 +591,7 @@ struct AttnArgs {
   const uint16_t* kv;
   const int32_t* page_table;
   int M, pos0, G, hkv, max_pages;
-  float qscale;
+  float scale, qscale;        // 1 / sqrt(dh), and the same times log2(e)
 };
 
 template <int DH>
@@ -598,6 +601,7 @@ __global__ __launch_bounds__(kWG, 2) void k_pf_attn(AttnArgs A) {
   constexpr int KPT = KT * NCH / kWG;          // K chunks per thread (one page each pass)
   constexpr int VTH = KT / 4 * (DH / 8);       // threads with a 4 x 8 block of V
   extern __shared__ __align__(16) char plds[];
+  __shared__ uint32_t s_nan[kWG / 64];  // per wave, its queries whose result is NaN
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, col = lane & 31, h = lane >> 5;
   const int g = blockIdx.x, G = A.G, rpw = 128 / G;
   const int row0 = ((int)gridDim.y - 1 - (int)blockIdx.y) * rpw;  // the longest rows first
@@ -760,15 +764,36 @@ __global__ __launch_bounds__(kWG, 2) void k_pf_attn(AttnArgs A) {
     }
     if (more) store_v(buf ^ 1, t + 1);
   }
-  if (row0 + qi / G >= A.M) return;
-  const float inv = 1.0f / l_run;
-  const size_t at = (size_t)qr * qd + (size_t)qh * DH + 4 * h;
+  bool nan = l_run != l_run;
 #pragma unroll
   for (int tt = 0; tt < NT; tt++)
 #pragma unroll
-    for (int v = 0; v < 16; v += 4)
-      store_planes4(A.out, at + tt * 32 + 2 * v, o[tt][v] * inv, o[tt][v + 1] * inv, o[tt][v + 2] * inv,
-                    o[tt][v + 3] * inv);
+    for (int v = 0; v < 16; v++) nan = nan || o[tt][v] != o[tt][v];
+  const bool mine = row0 + qi / G < A.M;
+  const unsigned long long nans = __ballot(nan && mine);
+  if (lane == 0) s_nan[w] = (uint32_t)nans | (uint32_t)(nans >> 32);
+  if (mine) {
+    const float inv = 1.0f / l_run;
+    const size_t at = (size_t)qr * qd + (size_t)qh * DH + 4 * h;
+#pragma unroll
+    for (int tt = 0; tt < NT; tt++)
+#pragma unroll
+      for (int v = 0; v < 16; v += 4)
+        store_planes4(A.out, at + tt * 32 + 2 * v, o[tt][v] * inv, o[tt][v + 1] * inv, o[tt][v + 2] * inv,
+                      o[tt][v + 3] * inv);
+  }
+  __syncthreads();  // every wave's queries are stored, and the key tiles are free
+  for (int ww = 0; ww < kWG / 64; ww++)
+    for (uint32_t m = __builtin_amdgcn_readfirstlane(s_nan[ww]); m != 0u; m &= m - 1u) {
+      const int j = ww * 32 + __builtin_ctz(m), row = row0 + j / G;
+      const size_t at = (size_t)row * qd + (size_t)(g * G + j % G) * DH;
+      float a[4], M, L;
+      if (attn_query_plain<DH>(A.kv, A.page_table, A.hkv, g, A.q + at, A.scale, 0, A.pos0 + row + 1,
+                               reinterpret_cast<float*>(plds), M, L, a)) {
+        const float inv = 1.0f / L;
+        store_planes4(A.out, at + 4 * (tid % (DH / 4)), a[0] * inv, a[1] * inv, a[2] * inv, a[3] * inv);
+      }
+    }
 }
 
 // ---------------------------------------------------------------------------------------- launches
@@ -955,6 +980,7 @@ void prefill_mfma(const Ctx& C, const PrefillBufs& B, const LayerDesc* layers, i
       A.G = C.G;
       A.hkv = C.hkv;
       A.max_pages = C.max_pages;
+      A.scale = C.scale;
       A.qscale = C.scale * 1.44269504088896340736f;
       attention(C, A, s);
       plain(pa, rows, C.qdim, L.wo, C.qdim);
