@@ -582,9 +582,10 @@ __global__ __launch_bounds__(kWG) void k_pdm_attn_merge(Ctx C, Planes out) {
 // A workgroup's rows share its key tiles, so 0 * v of a value past a row's own position, or 0 * k of a query
 // plane, makes NaN of a row whose own keys and values do not: a query that ends as NaN is computed again over
 // its own keys by plain FMAs (attn_query_plain).
-// Bound: MFMA (48 per 32 keys) beside the softmax's vector work. A layer of the 4B class takes 34 us at
-// 384 rows and 105 us at 1501; the wide model's 2048-row chunks at 6000 tokens 225 us (46, 147 and 343
-// with the page of each tile read where it is used, behind the keys in flight).
+// Bound: MFMA (48 per 32 keys) beside the softmax's vector work. A layer of the 4B class takes 37 us for 384
+// rows and 102 + 60 us for the chunks of 768 and 733 rows of 1501; the wide model's chunks of 2048, 2048 and
+// 1904 rows 134, 249 and 356 us. With the page of each tile read where it is used, behind the keys in flight,
+// they took 1.3 to 1.5 times as long.
 struct AttnArgs {
   const float* q;
   Planes out;                 // [M][Hq*dh]
@@ -592,7 +593,17 @@ struct AttnArgs {
   const int32_t* page_table;
   int M, pos0, G, hkv, max_pages;
   float scale, qscale;        // 1 / sqrt(dh), and the same times log2(e)
+  float4* tot;                // sums of earlier segments: a wave's [DH/8][64 lanes], then its (m, l)
 };
+
+// Key tiles of a segment, after which the sums restart from zero and the segment's join those before it, kept
+// in global memory (the registers hold one set). One accumulator over the whole prompt rounds every product's
+// sum at the running total's magnitude; relative error on flat scores (and at scores of deviation 1.5):
+//   keys       one accumulator       256-key segments      fp32 MFMA, splits of 128 keys
+//   1501       1.6e-7 (3.8e-7)       1.2e-7 (3.4e-7)       1.3e-7 (5.7e-7)
+//   6000       2.8e-7 (5.2e-7)       1.3e-7 (3.9e-7)       1.4e-7 (6.4e-7)
+// 512-key segments are at 1.6e-7 at 6000 keys. expf and a scale without log2(e) change none of these figures.
+constexpr int kPfSeg = 4;
 
 template <int DH>
 __global__ __launch_bounds__(kWG, 2) void k_pf_attn(AttnArgs A) {
@@ -600,6 +611,7 @@ __global__ __launch_bounds__(kWG, 2) void k_pf_attn(AttnArgs A) {
   constexpr int KBUF = KT * DH * 2, VBUF = DH * KT * 2, BUF = KBUF + VBUF;
   constexpr int KPT = KT * NCH / kWG;          // K chunks per thread (one page each pass)
   constexpr int VTH = KT / 4 * (DH / 8);       // threads with a 4 x 8 block of V
+  constexpr int UB = DH == 64 ? 2 : 1;         // 32-key blocks unrolled: at 128 dims two spill
   extern __shared__ __align__(16) char plds[];
   __shared__ uint32_t s_nan[kWG / 64];  // per wave, its queries whose result is NaN
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, col = lane & 31, h = lane >> 5;
@@ -685,6 +697,41 @@ __global__ __launch_bounds__(kWG, 2) void k_pf_attn(AttnArgs A) {
 #pragma unroll
   for (int t = 0; t < NT; t++) o[t] = (f32x16)(0.f);
   float m_run = -INFINITY, l_run = 0.f;
+  // the earlier segments' sums join this one's; keep: the result goes back and this segment's sums start over
+  auto fold = [&](bool first, bool keep) {
+    float4* tot = A.tot + (((size_t)blockIdx.y * gridDim.x + blockIdx.x) * (kWG / 64) + wu) * ((NT * 4 + 1) * 64) + lane;
+    float al = 0.f;
+    if (!first) {
+      const float2 ml = *reinterpret_cast<const float2*>(tot + NT * 4 * 64);
+      al = __builtin_amdgcn_exp2f(ml.x - m_run);
+      l_run = fmaf(ml.y, al, l_run);
+    }
+#pragma unroll
+    for (int tt = 0; tt < NT; tt++) {
+      if (!first) {
+        float4 x[4];
+#pragma unroll
+        for (int i = 0; i < 4; i++) x[i] = tot[(tt * 4 + i) * 64];
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+          o[tt][4 * i] = fmaf(x[i].x, al, o[tt][4 * i]);
+          o[tt][4 * i + 1] = fmaf(x[i].y, al, o[tt][4 * i + 1]);
+          o[tt][4 * i + 2] = fmaf(x[i].z, al, o[tt][4 * i + 2]);
+          o[tt][4 * i + 3] = fmaf(x[i].w, al, o[tt][4 * i + 3]);
+        }
+      }
+      if (keep) {
+#pragma unroll
+        for (int i = 0; i < 4; i++)
+          tot[(tt * 4 + i) * 64] = make_float4(o[tt][4 * i], o[tt][4 * i + 1], o[tt][4 * i + 2], o[tt][4 * i + 3]);
+        o[tt] = (f32x16)(0.f);
+      }
+    }
+    if (keep) {
+      *reinterpret_cast<float2*>(tot + NT * 4 * 64) = make_float2(m_run, l_run);
+      l_run = 0.f;
+    }
+  };
 
   int pg = pages(0);
   issue_k(0, pg);
@@ -702,7 +749,7 @@ __global__ __launch_bounds__(kWG, 2) void k_pf_attn(AttnArgs A) {
     }
     const char* kt = plds + buf * BUF;
     const char* vt = kt + KBUF;
-#pragma unroll
+#pragma unroll UB
     for (int b = 0; b < 2; b++) {  // 32 keys at a time
       const int key = b * 32 + col;
       f32x16 s;
@@ -762,8 +809,10 @@ __global__ __launch_bounds__(kWG, 2) void k_pf_attn(AttnArgs A) {
       }
       l_run += ps + __shfl_xor(ps, 32, 64);
     }
+    if (more && (t + 1) % kPfSeg == 0) fold(t + 1 == kPfSeg, true);
     if (more) store_v(buf ^ 1, t + 1);
   }
+  if (tiles > kPfSeg) fold(false, false);
   bool nan = l_run != l_run;
 #pragma unroll
   for (int tt = 0; tt < NT; tt++)
@@ -981,6 +1030,7 @@ void prefill_mfma(const Ctx& C, const PrefillBufs& B, const LayerDesc* layers, i
       A.hkv = C.hkv;
       A.max_pages = C.max_pages;
       A.scale = C.scale;
+      A.tot = reinterpret_cast<float4*>(B.part);  // free here; fits: rows (a multiple of 128) * qdim * 9/8 floats at most
       A.qscale = C.scale * 1.44269504088896340736f;
       attention(C, A, s);
       plain(pa, rows, C.qdim, L.wo, C.qdim);
