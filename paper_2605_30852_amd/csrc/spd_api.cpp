@@ -30,6 +30,7 @@ struct Layout {
   size_t ktrace;
   size_t pfpx, pfpart, pfrs, pfpa, pfpb, pfzero;  // prefill of bf16 models
   int pf_rows;
+  size_t pf_part;  // floats at pfpart
   size_t su, swlog, swgmax, sqids, sqp, sqcnt, spq;  // sampled decoding
   size_t total;
   int wlog_stride;
@@ -126,10 +127,12 @@ Layout make_layout(const spd_config& c) {
   L.anch = take(sizeof(float) * n * n * d);
   L.pdmx = take(sizeof(float) * kMaxRows * d);
   if (c.dtype == SPD_BF16) {  // chunks on matrix cores
-    const size_t R = L.pf_rows = prefill_rows(c.max_tokens, d, c.ffn_dim, qdim, qdim + 2 * hkv * dh);
+    const int qkv = qdim + 2 * hkv * dh, chunk_rows = prefill_chunk_rows(d, c.ffn_dim, qdim, qkv);
+    const size_t R = L.pf_rows = std::min(chunk_rows, (c.max_tokens + 127) / 128 * 128);
+    L.pf_part = prefill_part_floats(chunk_rows, d, c.ffn_dim, qkv);
     L.pfx = take(sizeof(float) * R * d);
     L.pfpx = take(sizeof(float) * R * d);
-    L.pfpart = take(sizeof(float) * prefill_part_floats(R, d, c.ffn_dim, qdim + 2 * hkv * dh));
+    L.pfpart = take(sizeof(float) * L.pf_part);
     L.pfrs = take(sizeof(float) * R);
     L.pfpa = take(sizeof(uint16_t) * 3 * R * std::max(d, qdim));
     // SwiGLU planes and raw stage inputs; the queries live between the two
@@ -654,7 +657,7 @@ spd_status spd_init(const spd_config* cfg, const spd_weights* w, void* workspace
   if (h->bf16) {
     PrefillBufs& P = h->pf;
     P.rows = lay.pf_rows;
-    P.part_cap = prefill_part_floats(P.rows, c.d_model, c.ffn_dim, C.qdim + 2 * C.kvdim);
+    P.part_cap = lay.pf_part;
     P.x = C.pf_x;
     P.px = (float*)(ws + lay.pfpx);
     P.q = (float*)(ws + lay.pfpb);

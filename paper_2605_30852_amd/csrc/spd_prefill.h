@@ -23,7 +23,7 @@ struct Planes {
 
 // Scratch of the prefill, and of the draft module in a step (in the workspace).
 struct PrefillBufs {
-  int rows;          // row capacity, a multiple of 128
+  int rows;          // row capacity, a multiple of 128: a chunk's, or max_tokens' where that is less
   size_t part_cap;   // floats in part
   float* x;          // [rows][d] residual rows of the target
   float* px;         // [rows][d] residual rows of the draft module
@@ -35,8 +35,10 @@ struct PrefillBufs {
   uint16_t* zeros;   // 256 bytes of zeros
 };
 
-int prefill_rows(int max_tokens, int d, int F, int qdim, int qkv_cols);
-size_t prefill_part_floats(int rows, int d, int F, int qkv_cols);
+// Rows of a chunk and floats of partial sums for a model. Neither depends on a handle's max_tokens: the K splits
+// follow from the partial sums that fit, and handles of any capacity store the same bits for a prompt.
+int prefill_chunk_rows(int d, int F, int qdim, int qkv_cols);
+size_t prefill_part_floats(int chunk_rows, int d, int F, int qkv_cols);
 
 // The whole prompt: C.tok[0, len) through the target and the draft module's caches; the last row's
 // residual ends in row *last_row of B.x. Asynchronous on stream.

@@ -937,14 +937,14 @@ void attention(const Ctx& C, AttnArgs A, hipStream_t s) {
 
 }  // namespace
 
-int prefill_rows(int max_tokens, int d, int F, int qdim, int qkv_cols) {
+int prefill_chunk_rows(int d, int F, int qdim, int qkv_cols) {
   auto bytes = [&](size_t rows) {
     return 4 * (2 * rows * d + prefill_part_floats((int)rows, d, F, qkv_cols) + rows) + 6 * rows * std::max(d, qdim) +
            std::max(6 * rows * std::max(d, F), 4 * rows * qdim);
   };
   int rows = kPrefillRows;
   while (rows > kPrefillMinRows && bytes(rows) > kPrefillBytes) rows -= 128;
-  return std::min(rows, (max_tokens + 127) / 128 * 128);
+  return rows;
 }
 
 // Partial sums: four splits of the narrow projections and two of QKV over a full chunk, and four of the

@@ -63,3 +63,24 @@ def test_prefill_caches_and_logits(shape, P):
     assert want[first] >= want.max() - 2 * err
     eng.close()
     print(f"  worst cache row {worst:.2e}, logits {err:.2e}", file=sys.stderr, flush=True)
+
+
+@pytest.mark.parametrize("P", [40, 200, 300, 500])
+def test_prefill_does_not_depend_on_capacity(P):
+    """Handles that differ in max_tokens only store the same bits for a prompt: every layer's keys and values, and
+    the first logits. 193 to 1024 rows of this width have K splits that the partial sums' space can cut short."""
+    from paper_2605_30852_amd.engine import DeviceWeights, Engine
+    w = DeviceWeights(WIDE3, SEED)
+    prompt = synth.prompt(WIDE3, SEED + P, P)
+    got = []
+    for cap in (P + 8, 1024, 4096):
+        print(f"[capacity {cap} P={P}]", file=sys.stderr, flush=True)
+        eng = Engine(w, max_tokens=cap, attn_chunk=64)
+        eng.spd_set_debug(True)
+        eng.spd_prefill(prompt)
+        got.append([eng.exit_logits()] + [x for pdm, n in ((False, WIDE3.n_layers), (True, WIDE3.pdm_layers))
+                                          for l in range(n) for x in eng.kv(l, 0, P, pdm=pdm)])
+        eng.close()
+    for other in got[1:]:
+        for i, (a, b) in enumerate(zip(got[0], other)):
+            assert np.array_equal(a, b), (P, i)
