@@ -19,6 +19,8 @@
 // 32 splits issued at once. The split size is a function of the configuration only, so a token's
 // result never depends on how many stages run.
 #pragma once
+#include <type_traits>
+
 #include "spd_devfn.h"
 
 namespace spd {
@@ -187,7 +189,10 @@ __device__ __forceinline__ void attn_merge(const float* rec_base, int nsplit, in
         }
       }
       const float inv = 1.0f / L;
-      out((size_t)qi * DH + 2 * dp, a0 * inv, a1 * inv);
+      if constexpr (std::is_same<Out, float*>::value)
+        *reinterpret_cast<float2*>(out + qi * DH + 2 * dp) = make_float2(a0 * inv, a1 * inv);
+      else
+        out((size_t)qi * DH + 2 * dp, a0 * inv, a1 * inv);
     }
   }
 }
@@ -424,7 +429,7 @@ __device__ bool attn_split_g(const Ctx& C, const KVT* kvb, const float* q, float
   __syncthreads();
   if (!s_last) return false;
 
-  attn_merge<DH, true>(rec_base, nsplit, G, FloatOut{out}, reinterpret_cast<float*>(lbase + LA::kQ));
+  attn_merge<DH, true>(rec_base, nsplit, G, out, reinterpret_cast<float*>(lbase + LA::kQ));
   if (tid == 0) __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   return true;
 }
