@@ -288,9 +288,9 @@ spd_status spd_probe_hbm_read(const void* buf, size_t bytes, float* sink, int32_
  * group's stream, before (2) or after (3) that group's stage launches. SPD_E_INVAL otherwise. */
 spd_status spd_set_pdm_placement(spd_handle* h, int32_t place);
 
-/* Workgroups, at most, of each of the PDM's projection launches in a step (0: the default: fp32 models 32
- * per 256 MB of PDM weights, since their launches hold a CU's LDS beside the stage compute; bf16 models no
- * cap). */
+/* Workgroups, at most, of each of the PDM's projection launches in a step (0: the default, which follows
+ * the model: 32 per 256 MB of PDM weights where the module's rows go through vector GEMVs, since their
+ * launches hold a CU's LDS beside the stage compute; no cap where they go through matrix cores). */
 spd_status spd_set_pdm_grid(spd_handle* h, int32_t wgs);
 
 /* Launch trace: while on, every step first resets the trace and its stage launches, LM head, verify

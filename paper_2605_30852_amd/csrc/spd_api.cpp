@@ -189,6 +189,8 @@ struct spd_handle {
   PrefillBufs pf = {};  // bf16 models
   int dev = 0;
   int bf16 = 0;
+  bool pdm_vec = false;  // the draft module's rows take the vector GEMVs (pdm_vector)
+  int pdm_wgs = 0;       // spd_set_pdm_grid (0: the default)
   int J = 0;  // layer slots per step = longest stage
   hipStream_t main = nullptr, pdm = nullptr;
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
@@ -278,15 +280,36 @@ static void enqueue_layer(const Ctx& C, const Rows& r, hipStream_t s, spd_handle
   { TimedLaunch t(h, s, SPD_K_DOWN); Launch<WT>::down(C, r, s); }
 }
 
-// PDM GEMV workgroups. fp32: kRowsWGsDefault per 256 MB of PDM weights (feature projection and decoder
-// layers), so that a larger draft module keeps finishing inside the stage compute. bf16: no cap (each
-// launch is short and streams near the memory's rate).
-static int default_rows_wgs(const spd_config& c) {
-  if (c.dtype == SPD_BF16) return 0;
-  const double esz = 4.0;
+static double layer_bytes(const spd_config& c) {
   const double d = c.d_model, qd = (double)c.n_q_heads * c.head_dim, kvd = (double)c.n_kv_heads * c.head_dim;
-  const double layer = d * (qd + 2 * kvd) + qd * d + 3 * d * c.ffn_dim;
-  const double bytes = esz * (d * c.n_stages * d + c.pdm_layers * layer);
+  return (c.dtype == SPD_BF16 ? 2.0 : 4.0) * (d * (qd + 2 * kvd) + qd * d + 3 * d * c.ffn_dim);
+}
+
+// Whether the draft module's rows go through the vector GEMVs (RowBlocks: five launches a layer, slow ones) and
+// not through the matrix-core row GEMMs (ten short ones). Beside the stage compute every launch holds up the
+// stages' by some 3 us, and the vector form's time does not count while the stages hide it. Both sides of the
+// rule are in slots of five narrow stage launches, some 40 us: a draft layer takes 1 + rows / 4 of them, more
+// with its weights (few workgroups stream them), and the stages J, more where their weights are large. Measured,
+// vector against matrix cores, us per 16 steps (24 at 4B class):
+//   384 wide, n = 2: 3218 / 3543, with two draft layers 3381 / 4106; n = 4: 2400 / 2753, 3537 / 3381; n = 6: 2504 / 2118
+//   1024 wide, n = 1: 7812 / 8017, 7652 / 8045; n = 2: 4665 / 4856, 6902 / 5456; n = 3: 4364 / 4087; n = 8: 7133 / 2943
+//   4B class, n = 2 (12 steps): 22097 / 22268; n = 3: 38799 / 39191; n = 4: 33850 / 34103 (36691 / 36573 at 2048
+//   tokens); n = 6: 31960 / 30792.
+// fp32 models have the vector form only.
+static bool pdm_vector(const spd_config& c) {
+  if (c.dtype != SPD_BF16) return true;
+  const double mb = layer_bytes(c) / 1e6, n = c.n_stages;
+  const double slots = (c.n_layers + c.n_stages - 1) / c.n_stages;
+  return c.pdm_layers * (1.0 + n / 4) * (1.0 + mb / 14) <= 1.4 + slots * (1.0 + n * mb / 520);
+}
+
+// Workgroups, at most, of the draft module's projection launches. Vector form: kRowsWGsDefault per 256 MB of its
+// weights (feature projection and decoder layers), so that a larger one keeps finishing inside the stage compute.
+// Matrix cores: no cap (each launch is short and streams near the memory's rate).
+static int default_rows_wgs(const spd_config& c, bool vec) {
+  if (!vec) return 0;
+  const double esz = c.dtype == SPD_BF16 ? 2.0 : 4.0, d = c.d_model, layer = layer_bytes(c);
+  const double bytes = esz * d * c.n_stages * d + c.pdm_layers * layer;
   const int units = std::max(1, (int)std::lround(bytes / (256.0 * 1024 * 1024)));
   return std::min(kRowsWGsDefault * units, 1024);
 }
@@ -331,15 +354,20 @@ static spd_status enqueue_step(spd_handle* h, int forced_override) {
   // Pipeline Draft Module: pre-step features only (Section 3.3), so it can run beside the stage
   // compute; it ends by recording ev_join, which the LM head waits for. Its launches, in order: the
   // feature projection, the PDM layers, the draft head if not fused.
+  // post-step schedule: the PDM waits for the stage compute, which then hides nothing. At one stage the deeper
+  // features are the same ones, and it need not wait.
+  const bool serial = C.post_step && h->cfg.n_stages > 1;
+  const bool vec = !h->bf16 || (h->pdm_vec && !serial);
   auto enqueue_pdm = [&](hipStream_t s) -> spd_status {
     h->cur_slot = 0;
-    if constexpr (std::is_same<WT, uint16_t>::value) {
-      pdm_rows_mfma(C, h->pf, h->layer_desc.data(), h->cfg.n_stages, C.rows_wgs, s);
+    const int wgs = h->pdm_wgs > 0 ? h->pdm_wgs : default_rows_wgs(h->cfg, vec);
+    if (!vec) {
+      pdm_rows_mfma(C, h->pf, h->layer_desc.data(), h->cfg.n_stages, wgs, s);
     } else {
-      RowsF32::pdm_fc(C, 0, 0, s);
+      RowBlocks<WT>::pdm_fc(C, 0, 0, s);
       for (int l = 0; l < h->cfg.pdm_layers; l++)
-        RowsF32::layer(C, rows_block(h->cfg.n_layers + l, -1, -1, C.pdm_x, nullptr, -1, 1), h->cfg.n_stages,
-                       C.rows_wgs, s);
+        RowBlocks<WT>::layer(C, rows_block(h->cfg.n_layers + l, -1, -1, C.pdm_x, nullptr, -1, 1), h->cfg.n_stages,
+                             wgs, s);
     }
     if (!fused) {
       if (C.sam.top_k > 0)  // the draft module's distribution, left for the exit row's pass
@@ -352,8 +380,8 @@ static spd_status enqueue_step(spd_handle* h, int forced_override) {
     return SPD_OK;
   };
   const bool stage_streams = h->step_mode == 2;
-  // post-step schedule: the PDM waits for the stage compute (placement 5, on main_stream after it)
-  const int place = !h->pdm_on ? -1 : C.post_step ? 5 : stage_streams ? h->pdm_place : (h->pdm_place == 1 ? 1 : 0);
+  // place 5: on main_stream after the stage compute
+  const int place = !h->pdm_on ? -1 : serial ? 5 : stage_streams ? h->pdm_place : (h->pdm_place == 1 ? 1 : 0);
   if (place == -1) {  // no PDM launches: the join is satisfied at the fork
     if (sp) HIPC(hipEventRecord(sp[1], h->main));
     HIPC(hipEventRecord(h->ev_join, h->main));
@@ -475,17 +503,17 @@ static spd_status enqueue_prefill_f32(spd_handle* h, int len) {
   const int n = h->cfg.n_stages, L = h->cfg.n_layers;
   for (int t0 = 0; t0 < len; t0 += kMaxRows) {
     const int rc = std::min(kMaxRows, len - t0);
-    RowsF32::embed(C, t0, rc, h->main);
+    RowBlocks<float>::embed(C, t0, rc, h->main);
     for (int l = 0; l < L; l++) {
       int cap = -1;
       for (int s = 0; s + 1 <= n - 1; s++)
         if (l + 1 == C.beta[s + 1]) cap = s + 1;
-      RowsF32::layer(C, rows_block(l, rc, t0, C.pf_x, C.pf_anch, cap, 0), kMaxRows, 0, h->main);
+      RowBlocks<float>::layer(C, rows_block(l, rc, t0, C.pf_x, C.pf_anch, cap, 0), kMaxRows, 0, h->main);
     }
     // PDM KV over the prompt: every prompt row has full depth
-    RowsF32::pdm_fc(C, 1, rc, h->main);
+    RowBlocks<float>::pdm_fc(C, 1, rc, h->main);
     for (int i = 0; i < h->cfg.pdm_layers; i++)
-      RowsF32::layer(C, rows_block(L + i, rc, t0, C.pdm_x, nullptr, -1, 1), kMaxRows, 0, h->main);
+      RowBlocks<float>::layer(C, rows_block(L + i, rc, t0, C.pdm_x, nullptr, -1, 1), kMaxRows, 0, h->main);
     if (t0 + rc == len) enqueue_first_token<WT>(h, rc - 1, len);
     spd_status st = launch_check(h, "prefill");
     if (st != SPD_OK) return st;
@@ -614,7 +642,7 @@ spd_status spd_init(const spd_config* cfg, const spd_weights* w, void* workspace
   C.ls = c.pdm_layers;
   C.page = c.page_size;
   C.chunk = lay.chunk;
-  C.rows_wgs = default_rows_wgs(c);
+  h->pdm_vec = pdm_vector(c);
   C.max_pages = lay.num_pages;
   C.max_splits = lay.max_splits;
   C.max_tokens = c.max_tokens;
@@ -842,7 +870,7 @@ spd_status spd_set_pdm_placement(spd_handle* h, int32_t place) {
 
 spd_status spd_set_pdm_grid(spd_handle* h, int32_t wgs) {
   if (!h || wgs < 0 || wgs > 65535) return SPD_E_INVAL;
-  h->ctx.rows_wgs = wgs > 0 ? wgs : default_rows_wgs(h->cfg);
+  h->pdm_wgs = wgs;
   drop_graph(h);  // kernel arguments changed
   return SPD_OK;
 }

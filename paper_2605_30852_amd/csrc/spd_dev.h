@@ -70,7 +70,7 @@ enum StepKind { SK_QKV = 0, SK_ATTN = 1, SK_OPROJ = 2, SK_GATEUP = 3, SK_DOWN = 
 // chain after another; two groups keep every chain running from the fork.
 constexpr int kStageGroupsDefault = 2;
 constexpr int kStreamWGs = 1024;  // workgroups of one streaming stage launch (all its stages)
-// fp32 PDM row-block GEMV launches run beside the stage compute: a few workgroups, so that most CUs (and
+// PDM row-block GEMV launches (vector form) run beside the stage compute: a few workgroups, so that most CUs (and
 // their LDS) stay with the stage launches.
 constexpr int kRowsWGsDefault = 32;
 // Sampled decoding (top-k, temperature): at most this many tokens per distribution; a sampled
@@ -133,7 +133,6 @@ struct Ctx {
   BufSet b[2];      // 0: target stream, 1: PDM stream
   unsigned long long* ktrace;  // null, or the launch trace: per slot (first start, last end) wall clock
   int stream_wgs;   // workgroups of one streaming stage launch (all its stages)
-  int rows_wgs;     // at most this many workgroups per PDM projection launch (0: no cap)
   int J;            // layer slots per step (longest stage)
   Sampler sam;      // sampled decoding (sam.top_k == 0: greedy)
   int post_step;    // 1: the PDM reads the features after the step's stage compute (one stage deeper)
@@ -184,9 +183,11 @@ struct Launch {
   static void head_sample(const Ctx& c, int src, int row, int pos, int forced_override, int auto_rb,
                           void* stream);
 };
-// Row blocks of fp32 models (bf16 models' go through spd_prefill.h): the draft module's rows in a step and
-// the prefill's 8-row chunks.
-struct RowsF32 {
+// Row blocks through vector GEMVs: the draft module's rows in a step (fp32 models, and bf16 models whose draft
+// module is small beside the stages; the others go through spd_prefill.h) and the 8-row prefill chunks of fp32
+// models.
+template <typename WT>
+struct RowBlocks {
   // One decoder layer of a row block whose rows share the layer (at most max_rows rows): streaming GEMVs
   // applying each weight pair to all rows (the down projection also captures the rows' anchor when
   // r.anch and r.cap name one), and the rows' decode attention. Five launches; the GEMV launches take at

@@ -1427,26 +1427,27 @@ static void rgemv_launch(const Ctx& c, const Rows& r, int npairs, int K, int max
     launch_timed((k_rgemv<WT, KIND, 8>), grid, dim3(kWG), shm, S(s), c, r, nrp);
 }
 
-void RowsF32::layer(const Ctx& c, const Rows& r, int max_rows, int cap_wgs, void* s) {
+template <typename WT>
+void RowBlocks<WT>::layer(const Ctx& c, const Rows& r, int max_rows, int cap_wgs, void* s) {
   max_rows = std::max(1, std::min(max_rows, kMaxRows));
-  rgemv_launch<float, SG_QKV>(c, r, (c.hq + 2 * c.hkv) * (c.dh / 2), c.d, max_rows, cap_wgs, s);
+  rgemv_launch<WT, SG_QKV>(c, r, (c.hq + 2 * c.hkv) * (c.dh / 2), c.d, max_rows, cap_wgs, s);
   const int groups8 = (c.max_splits * c.hkv + 7) / 8 * 8;  // see k_attn_rows: XCD-aware order
   const dim3 agrid(groups8 * max_rows);
   const bool g4 = c.G <= 4;
   if (c.dh == 128) {
     if (g4)
-      launch_timed((k_attn_rows<float, 128, 4>), agrid, dim3(kWG), attn_split_lds<float, 128>(), S(s), c, r, max_rows);
+      launch_timed((k_attn_rows<WT, 128, 4>), agrid, dim3(kWG), attn_split_lds<WT, 128>(), S(s), c, r, max_rows);
     else
-      launch_timed((k_attn_rows<float, 128, 8>), agrid, dim3(kWG), attn_split_lds<float, 128>(), S(s), c, r, max_rows);
+      launch_timed((k_attn_rows<WT, 128, 8>), agrid, dim3(kWG), attn_split_lds<WT, 128>(), S(s), c, r, max_rows);
   } else {
     if (g4)
-      launch_timed((k_attn_rows<float, 64, 4>), agrid, dim3(kWG), attn_split_lds<float, 64>(), S(s), c, r, max_rows);
+      launch_timed((k_attn_rows<WT, 64, 4>), agrid, dim3(kWG), attn_split_lds<WT, 64>(), S(s), c, r, max_rows);
     else
-      launch_timed((k_attn_rows<float, 64, 8>), agrid, dim3(kWG), attn_split_lds<float, 64>(), S(s), c, r, max_rows);
+      launch_timed((k_attn_rows<WT, 64, 8>), agrid, dim3(kWG), attn_split_lds<WT, 64>(), S(s), c, r, max_rows);
   }
-  rgemv_launch<float, SG_OPROJ>(c, r, (c.d + 1) / 2, c.qdim, max_rows, cap_wgs, s);
-  rgemv_launch<float, SG_GATEUP>(c, r, c.F, c.d, max_rows, cap_wgs, s);
-  rgemv_launch<float, SG_DOWN>(c, r, (c.d + 1) / 2, c.F, max_rows, cap_wgs, s);
+  rgemv_launch<WT, SG_OPROJ>(c, r, (c.d + 1) / 2, c.qdim, max_rows, cap_wgs, s);
+  rgemv_launch<WT, SG_GATEUP>(c, r, c.F, c.d, max_rows, cap_wgs, s);
+  rgemv_launch<WT, SG_DOWN>(c, r, (c.d + 1) / 2, c.F, max_rows, cap_wgs, s);
 }
 
 template <typename WT>
@@ -1472,9 +1473,10 @@ void Launch<WT>::attn(const Ctx& c, const Rows& r, void* s) {
   }
 }
 
-void RowsF32::pdm_fc(const Ctx& c, int prefill, int nrows, void* s) {
+template <typename WT>
+void RowBlocks<WT>::pdm_fc(const Ctx& c, int prefill, int nrows, void* s) {
   const dim3 grid((c.d + 7) / 8);
-  launch_timed((k_pdm_fc<float>), grid, dim3(kWG), gemv_lds<float>(c.n * c.d, kMaxRows), S(s), c, prefill, nrows);
+  launch_timed((k_pdm_fc<WT>), grid, dim3(kWG), gemv_lds<WT>(c.n * c.d, kMaxRows), S(s), c, prefill, nrows);
 }
 
 // Workgroups of `fn` (with `lds` bytes of dynamic LDS) that the GPU holds at once.
@@ -1546,11 +1548,14 @@ void Launch<WT>::head_sample(const Ctx& c, int src, int row, int pos, int forced
                  auto_rb, lcap);
 }
 
-void RowsF32::embed(const Ctx& c, int t0, int nrows, void* s) {
-  launch_timed((k_embed_rows<float>), dim3(nrows), dim3(kWG), 0, S(s), c, t0, nrows);
+template <typename WT>
+void RowBlocks<WT>::embed(const Ctx& c, int t0, int nrows, void* s) {
+  launch_timed((k_embed_rows<WT>), dim3(nrows), dim3(kWG), 0, S(s), c, t0, nrows);
 }
 
 template struct Launch<float>;
+template struct RowBlocks<float>;
+template struct RowBlocks<uint16_t>;
 template struct Launch<uint16_t>;
 
 void launch_reseed(const Ctx& c, int keep, int tok, int prompt_len, void* s, int bf16) {
