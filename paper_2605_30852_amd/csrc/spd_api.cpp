@@ -152,8 +152,10 @@ Layout make_layout(const spd_config& c) {
     L.act[s] = take(sizeof(float) * kMaxRows * (size_t)c.ffn_dim);
     L.part[s] = take(sizeof(float) * part_floats);
     L.cnt[s] = take(sizeof(int32_t) * kMaxStages * hkv);
-    L.rpart[s] = take(sizeof(float) * rows_split_floats(c));
-    L.rtick[s] = take(sizeof(int32_t) * kRowSplitCols);
+    if (c.dtype == SPD_F32) {  // the prefill's row blocks
+      L.rpart[s] = take(sizeof(float) * rows_split_floats(c));
+      L.rtick[s] = take(sizeof(int32_t) * kRowSplitCols);
+    }
     L.hkey[s] = take(sizeof(unsigned long long));
   }
   L.nkslots = 5 * L.J * n + 4;
@@ -706,8 +708,10 @@ spd_status spd_init(const spd_config* cfg, const spd_weights* w, void* workspace
     B.act = (float*)(ws + lay.act[s]);
     B.part = (float*)(ws + lay.part[s]);
     B.cnt = (int32_t*)(ws + lay.cnt[s]);
-    B.rpart = (float*)(ws + lay.rpart[s]);
-    B.rtick = (int32_t*)(ws + lay.rtick[s]);
+    if (!h->bf16) {
+      B.rpart = (float*)(ws + lay.rpart[s]);
+      B.rtick = (int32_t*)(ws + lay.rtick[s]);
+    }
     B.hkey = (unsigned long long*)(ws + lay.hkey[s]);
   }
   C.post_step = 0;
@@ -774,7 +778,8 @@ spd_status spd_init(const spd_config* cfg, const spd_weights* w, void* workspace
   HIPI(hipMemsetAsync(ws + lay.tok, 0, sizeof(int32_t) * (c.max_tokens + 8), h->main));
   HIPI(hipMemsetAsync(ws + lay.forced, 0xff, sizeof(int32_t) * (c.max_tokens + 8), h->main));
   for (int s = 0; s < 2; s++) HIPI(hipMemsetAsync(ws + lay.cnt[s], 0, sizeof(int32_t) * kMaxStages * c.n_kv_heads, h->main));
-  for (int s = 0; s < 2; s++) HIPI(hipMemsetAsync(ws + lay.rtick[s], 0, sizeof(int32_t) * kRowSplitCols, h->main));
+  if (!h->bf16)
+    for (int s = 0; s < 2; s++) HIPI(hipMemsetAsync(ws + lay.rtick[s], 0, sizeof(int32_t) * kRowSplitCols, h->main));
   for (int s = 0; s < 2; s++) HIPI(hipMemsetAsync(ws + lay.hkey[s], 0, sizeof(unsigned long long), h->main));
   HIPI(hipMemsetAsync(ws + lay.sqcnt, 0, sizeof(int32_t) * c.n_stages, h->main));
   HIPI(hipMemsetAsync(ws + lay.spq, 0, (sizeof(int32_t) + sizeof(float)) * kMaxTopK + sizeof(int32_t), h->main));

@@ -14,6 +14,8 @@
 #include <hip/hip_runtime.h>
 #include <math.h>
 
+#include <type_traits>
+
 #include "spd_dev.h"
 #include "spd_devfn.h"
 #include "spd_gemv.h"
@@ -1393,24 +1395,26 @@ static int rows_per_pass(int K, int max_rows) {
 
 template <typename WT, int KIND>
 static void rgemv_launch(const Ctx& c, const Rows& r, int npairs, int K, int max_rows, int cap_wgs, void* s) {
-  const int rows = std::max(1, std::min(max_rows, kMaxRows));
-  const int min_cols = (npairs + 255) / 256;  // no wave streams more than 64 pairs
   // K-split (uncapped row blocks: the fp32 prefill's chunks): every chunk of every row in one pass over
   // the weights, a small LDS slice per workgroup. A capped launch (side work beside the stage compute)
   // keeps the full-width form: with few columns the split's last-arriver merges run long.
-  if (cap_wgs <= 0 && stream_lds<WT>(K) * rows > (size_t)kRowLdsBudget && K > kRowSplitK &&
-      min_cols <= kRowSplitCols) {
-    const int ns = (K + kRowSplitK - 1) / kRowSplitK;
-    const size_t shm = (size_t)rows * kRowSplitK * sizeof(float);
-    const int resident = dev_limits().cus * std::max(1, (int)((size_t)dev_limits().lds_max / (shm + 1024)));
-    const int cols = std::min(std::max(std::min(stream_grid(c, npairs, 1), std::max(1, resident / ns)), min_cols),
-                              kRowSplitCols);
-    const dim3 grid(cols, ns);
-    if (rows <= 4)
-      launch_timed((k_rgemv_ks<WT, KIND, 4>), grid, dim3(kWG), shm, S(s), c, r);
-    else
-      launch_timed((k_rgemv_ks<WT, KIND, 8>), grid, dim3(kWG), shm, S(s), c, r);
-    return;
+  if constexpr (std::is_same<WT, float>::value) {  // bf16 row blocks are always capped
+    const int rows = std::max(1, std::min(max_rows, kMaxRows));
+    const int min_cols = (npairs + 255) / 256;  // no wave streams more than 64 pairs
+    if (cap_wgs <= 0 && stream_lds<WT>(K) * rows > (size_t)kRowLdsBudget && K > kRowSplitK &&
+        min_cols <= kRowSplitCols) {
+      const int ns = (K + kRowSplitK - 1) / kRowSplitK;
+      const size_t shm = (size_t)rows * kRowSplitK * sizeof(float);
+      const int resident = dev_limits().cus * std::max(1, (int)((size_t)dev_limits().lds_max / (shm + 1024)));
+      const int cols = std::min(std::max(std::min(stream_grid(c, npairs, 1), std::max(1, resident / ns)), min_cols),
+                                kRowSplitCols);
+      const dim3 grid(cols, ns);
+      if (rows <= 4)
+        launch_timed((k_rgemv_ks<WT, KIND, 4>), grid, dim3(kWG), shm, S(s), c, r);
+      else
+        launch_timed((k_rgemv_ks<WT, KIND, 8>), grid, dim3(kWG), shm, S(s), c, r);
+      return;
+    }
   }
   const int nrp = rows_per_pass<WT>(K, max_rows);
   const size_t shm = stream_lds<WT>(K) * nrp;
