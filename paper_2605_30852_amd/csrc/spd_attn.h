@@ -307,14 +307,15 @@ __device__ bool attn_split_g(const Ctx& C, const KVT* kvb, const float* q, float
         }
       }
       // online softmax of head qq + 4j over the wave's keys (key 0 of the round is valid, so mn is
-      // finite for every head h < G)
+      // finite for every head h < G unless its scores are all -inf, which leaves l as it was, or NaN,
+      // which makes l NaN)
 #pragma unroll
       for (int j = 0; j < NJ; j++) {
         const int h = qq + 4 * j;
         const float mx = key_max(sel[j]);
         const float mn = fmaxf(m_run[j], mx);
         const float al = m_run[j] == -INFINITY ? 0.f : expf(m_run[j] - mn);
-        const float p = valid && h < G ? expf(sel[j] - mn) : 0.f;
+        const float p = sel[j] == -INFINITY ? 0.f : expf(sel[j] - mn);  // past the end, h >= G, or a score of -inf
         const float ps = key_sum(p);
         l_run[j] = l_run[j] * al + ps;
         m_run[j] = mn;
@@ -363,7 +364,7 @@ __device__ bool attn_split_g(const Ctx& C, const KVT* kvb, const float* q, float
   __syncthreads();
 
   // combine the waves in wave order: (A, M, L) of the split per (head, dimension pair); a wave with
-  // no key has m = -inf and weight 0 (wave 0 always has key k0, so M is finite)
+  // no key has l = 0 and weight 0 (a NaN l counts even where the wave's maximum is still -inf)
   constexpr int NW = LA::kWaves;
   constexpr int NPAIR = MAXQ * DH / 2;
   constexpr int PPT = (NPAIR + kWG - 1) / kWG;
@@ -382,10 +383,10 @@ __device__ bool attn_split_g(const Ctx& C, const KVT* kvb, const float* q, float
       for (int wv = 0; wv < NW; wv++) {
         const char* wb = lbase + LA::kQ + (size_t)wv * LA::kWave;
         const float* aw = reinterpret_cast<const float*>(wb + LA::kVt + LA::kP);
-        const float mw = aw[MAXQ + qi];
-        if (mw != -INFINITY) {
-          const float f = expf(mw - M);
-          L = fmaf(aw[2 * MAXQ + qi], f, L);
+        const float lw = aw[2 * MAXQ + qi];
+        if (lw != 0.f) {
+          const float f = expf(aw[MAXQ + qi] - M);
+          L = fmaf(lw, f, L);
           const float2 ov = *reinterpret_cast<const float2*>(reinterpret_cast<const float*>(wb) + qi * DH + 2 * dp);
           a0 = fmaf(ov.x, f, a0);
           a1 = fmaf(ov.y, f, a1);

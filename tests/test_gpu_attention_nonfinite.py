@@ -22,25 +22,37 @@ def _reference(q, k, v):
 @pytest.mark.parametrize("keys,chunk", [(40, 64), (130, 64), (163, 48)])
 @pytest.mark.parametrize("hq,hkv,dh", [(8, 2, 128), (8, 1, 64), (2, 2, 64)])
 def test_rows_see_their_own_nonfinite_keys(hq, hkv, dh, keys, chunk):
+    _rows_see_their_own(hq, hkv, dh, keys, chunk, torch.bfloat16)
+
+
+@pytest.mark.parametrize("keys,chunk", [(40, 64), (130, 64), (163, 48)])
+@pytest.mark.parametrize("hq,hkv,dh", [(8, 2, 128), (8, 1, 64)])
+def test_rows_of_fp32_caches_do(hq, hkv, dh, keys, chunk):
+    """The one-row split of fp32 caches, whose waves may hold a single key: a wave of nothing but NaN scores, or of
+    nothing but minus infinity, counts as such."""
+    _rows_see_their_own(hq, hkv, dh, keys, chunk, torch.float32)
+
+
+def _rows_see_their_own(hq, hkv, dh, keys, chunk, dtype):
     from paper_2605_30852_amd import binding as B
     rows, G, inf = 4, hq // hkv, float("inf")
     rng = np.random.default_rng(keys + dh)
     lens = np.array([keys - i for i in range(rows)], dtype=np.int32)
     pages = (keys + 15) // 16 + 1
-    bf = lambda a: torch.from_numpy(a.astype(np.float32)).bfloat16()  # noqa: E731
-    base = bf(rng.standard_normal((2, pages * 16, hkv, dh)))
+    base = torch.from_numpy(rng.standard_normal((2, pages * 16, hkv, dh)).astype(np.float32)).to(dtype)
     q = rng.standard_normal((rows, hq, dh)).astype(np.float32)
     table = rng.permutation(pages).astype(np.int32)
     marks = {"value of the longest row's last key": [(1, keys - 1, 0, 3, inf)],
              "value of every row": [(1, 7, hkv - 1, 5, -inf)],
              "key of every row": [(0, 9, 0, 0, inf)],
              "NaN key of two rows": [(0, keys - 2, 0, 1, float("nan"))],
+             "key of the longest row at minus infinity": [(0, keys - 1, 0, 0, -inf)],
              "past every row": [(0, keys, 0, 2, float("nan")), (1, keys, 0, 2, inf)]}
     for what, at in marks.items():
         kv = base.clone()
         for part, key, head, dim, x in at:
             kv[part, key, head, dim] = x
-        pool = torch.empty(pages, 2, hkv, 16, dh, dtype=torch.bfloat16)
+        pool = torch.empty(pages, 2, hkv, 16, dh, dtype=dtype)
         pool[torch.from_numpy(table).long()] = kv.view(2, pages, 16, hkv, dh).permute(1, 0, 3, 2, 4)
         pool_d, q_d, table_d = pool.cuda(), torch.from_numpy(q).cuda(), torch.from_numpy(table).cuda()
         out = torch.zeros(rows, hq, dh, device="cuda")
@@ -48,8 +60,8 @@ def test_rows_see_their_own_nonfinite_keys(hq, hkv, dh, keys, chunk):
         ws = torch.empty(nb + 256, dtype=torch.uint8, device="cuda")
         print(f"[{what}: {hq}/{hkv}x{dh} keys {keys} chunk {chunk}]", flush=True)
         B.spd_decode_attention(q_d.data_ptr(), pool_d.data_ptr(), table_d.data_ptr(), pages, lens, hq, hkv, dh,
-                               B.SPD_BF16, chunk, out.data_ptr(), (ws.data_ptr() + 255) // 256 * 256, nb,
-                               torch.cuda.current_stream().cuda_stream)
+                               B.SPD_BF16 if dtype == torch.bfloat16 else B.SPD_F32, chunk, out.data_ptr(),
+                               (ws.data_ptr() + 255) // 256 * 256, nb, torch.cuda.current_stream().cuda_stream)
         torch.cuda.synchronize()
         got, x = out.cpu().numpy(), kv.double().numpy()
         for i in range(rows):
