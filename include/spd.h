@@ -330,9 +330,11 @@ spd_status spd_kernel_timing(spd_handle* h, double* total_ms, int32_t* launches)
 spd_status spd_span_timing(spd_handle* h, double* stage_ms, double* pdm_ms, double* late_ms, int32_t* steps);
 
 /* Ragged paged decode attention (Section 3.1: every in-flight token attends, at its own position, over
- * the cache of the layer it is on) for up to 8 query rows of one layer, as a call of its own. It runs
- * the step's attention split code: one workgroup per (key split, KV head, row), the last split of a
- * (row, head) to finish merging its splits in split order.
+ * the cache of the layer it is on) for up to 8 query rows of one layer, as a call of its own. fp32 caches,
+ * and bf16 caches in calls of short splits: the step's attention split code, one workgroup per (key split,
+ * KV head, row), the last split of a (row, head) to finish merging its splits in split order. Other bf16
+ * calls: one workgroup per (key split, KV head, rows of up to 32 query heads) on matrix cores, then a merge
+ * launch where there are several splits. Which one follows from the sizes and lengths of the call.
  *   q: device fp32 [nrows][n_q_heads][head_dim], the rows' rotated queries (query head h reads KV
  *      head h / (n_q_heads / n_kv_heads)); scores are scaled by 1/sqrt(head_dim).
  *   kv: device, one layer's pool [num_pages][K, V][n_kv_heads][16 keys][head_dim] of dtype.
@@ -356,8 +358,8 @@ spd_status spd_decode_attention(const float* q, const void* kv, const int32_t* p
  * loops, harnesses that forbid allocation. The same arguments and results without the workspace: the
  * split records and tickets live in a static device array of the library, 8.5 MB (2048 split records
  * of head_dim 128, plus 8 KiB of tickets) on each GPU the library runs on, held until the process
- * ends. The call allocates nothing (no hipMalloc, no library allocation); it clears the tickets with a
- * fill kernel before the attention, so a captured call replays correctly. Every call on a GPU uses that
+ * ends. The call allocates nothing (no hipMalloc, no library allocation); where it uses tickets it clears
+ * them with a fill kernel before the attention, so a captured call replays correctly. Every call on a GPU uses that
  * GPU's one array and leaves its contents there: calls that overlap on one GPU (other streams, other
  * threads) race, so the caller serializes them. SPD_E_CAPACITY (before anything is launched) when
  * nrows * n_kv_heads * ceil(max lens / chunk) exceeds 2048; otherwise as spd_decode_attention. */

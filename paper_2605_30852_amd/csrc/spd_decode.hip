@@ -84,10 +84,23 @@ __global__ __launch_bounds__(kWG) void k_zero_i32(int* p, int n) {
 struct Request {
   Ctx C;
   RaggedRows R;
-  int nrows, smax, dh, g4, bf16;
+  int nrows, smax, dh, g4, bf16, vec;
   size_t rec_floats;  // split records
   int tickets;        // one per (row, KV head)
 };
+
+// bf16: whether the rows take the vector split, one workgroup per (key split, KV head, row) and the merge by
+// tickets, and not the matrix-core one with its merge launch. The vector form is the quicker one while a split is a
+// few rounds of 64 keys (fewer of them the more heads a round has), there are several splits to merge and
+// about one workgroup a CU: 8 rows of 300 keys, splits of 64, 8 and 2 heads of 128: 13.4 us against 16.1; 2 rows
+// of 1500 keys: 13.5 against 15.3; 8 rows, splits of 256: 16.4 against 18.8. Past that it is not: 8 rows of 1500
+// keys with 32 and 8 heads 30.5 against 19.4, 4 rows of 300 keys with 8 heads on one 25.0 against 19.7 (splits of
+// 256). At 64 dims the two differ by less than the call's own time varies.
+bool vector_form(const Request& r, int chunk) {
+  const int keys = r.nrows > 4 ? 1024 : r.nrows > 2 ? 512 : 256;
+  return r.dh == 128 && r.smax > 1 && r.nrows * r.smax > 8 && (long long)r.nrows * r.smax * r.C.hkv <= 320 &&
+         (long long)chunk * r.C.G <= keys;
+}
 
 spd_status check(const float* q, const void* kv, const int32_t* page_table, int32_t num_pages, const int32_t* lens,
                  int32_t nrows, int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim, int32_t dtype,
@@ -134,26 +147,27 @@ spd_status check(const float* q, const void* kv, const int32_t* page_table, int3
   r.dh = head_dim;
   r.g4 = G <= 4;
   r.bf16 = dtype == SPD_BF16;
+  r.vec = !r.bf16 || vector_form(r, chunk);
   r.rec_floats = (size_t)nrows * n_kv_heads * smax * kAttnMaxQ * (head_dim + 2);
   r.tickets = nrows * n_kv_heads;
   return SPD_OK;
 }
 
-template <int DH>
-void launch_ragged_f32(const Request& r, const float* q, const void* kv, float* out, float* part, int* cnt,
+template <typename KVT, int DH>
+void launch_ragged_vec(const Request& r, const float* q, const void* kv, float* out, float* part, int* cnt,
                        hipStream_t s) {
   const dim3 grid(r.smax, r.C.hkv, r.nrows);
-  const size_t shm = attn_split_lds<float, DH>();
+  const size_t shm = attn_split_lds<KVT, DH>();
   if (r.g4)
-    hipLaunchKernelGGL((k_attn_ragged<float, DH, 4>), grid, dim3(kWG), shm, s, r.C, q, (const float*)kv, out, part, cnt,
+    hipLaunchKernelGGL((k_attn_ragged<KVT, DH, 4>), grid, dim3(kWG), shm, s, r.C, q, (const KVT*)kv, out, part, cnt,
                        r.R, r.smax);
   else
-    hipLaunchKernelGGL((k_attn_ragged<float, DH, 8>), grid, dim3(kWG), shm, s, r.C, q, (const float*)kv, out, part, cnt,
+    hipLaunchKernelGGL((k_attn_ragged<KVT, DH, 8>), grid, dim3(kWG), shm, s, r.C, q, (const KVT*)kv, out, part, cnt,
                        r.R, r.smax);
 }
 
 template <int DH>
-void launch_ragged_bf16(const Request& r, const float* q, const void* kv, float* out, float* part, hipStream_t s) {
+void launch_ragged_mfma(const Request& r, const float* q, const void* kv, float* out, float* part, hipStream_t s) {
   const int rpg = 32 / r.C.G;
   const dim3 grid(r.smax, r.C.hkv, (r.nrows + rpg - 1) / rpg);
   hipLaunchKernelGGL((k_attn_ragged_mfma<DH>), grid, dim3(kWG), attn_mfma_lds<DH>(std::min(r.nrows, rpg) * r.C.G), s, r.C,
@@ -163,21 +177,23 @@ void launch_ragged_bf16(const Request& r, const float* q, const void* kv, float*
                        (const float*)part, r.R);
 }
 
-// bf16: the splits, then (with more than one) their merge. fp32: the tickets are cleared (a fill kernel,
-// so that a captured call replays correctly), then the attention, whose last splits merge.
+// Matrix cores: the splits, then (with more than one) their merge. Vector form: the tickets are cleared (a fill
+// kernel, so that a captured call replays correctly), then the attention, whose last splits merge.
 spd_status run(const Request& r, const float* q, const void* kv, float* out, float* part, int* cnt, void* stream) {
   hipStream_t s = (hipStream_t)stream;
-  if (r.bf16) {
+  if (!r.vec) {
     if (r.dh == 128)
-      launch_ragged_bf16<128>(r, q, kv, out, part, s);
+      launch_ragged_mfma<128>(r, q, kv, out, part, s);
     else
-      launch_ragged_bf16<64>(r, q, kv, out, part, s);
+      launch_ragged_mfma<64>(r, q, kv, out, part, s);
   } else {
     hipLaunchKernelGGL(k_zero_i32, dim3((r.tickets + kWG - 1) / kWG), dim3(kWG), 0, s, cnt, r.tickets);
-    if (r.dh == 128)
-      launch_ragged_f32<128>(r, q, kv, out, part, cnt, s);
+    if (r.bf16)
+      launch_ragged_vec<uint16_t, 128>(r, q, kv, out, part, cnt, s);
+    else if (r.dh == 128)
+      launch_ragged_vec<float, 128>(r, q, kv, out, part, cnt, s);
     else
-      launch_ragged_f32<64>(r, q, kv, out, part, cnt, s);
+      launch_ragged_vec<float, 64>(r, q, kv, out, part, cnt, s);
   }
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) {
