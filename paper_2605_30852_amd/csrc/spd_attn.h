@@ -1,5 +1,6 @@
-// Decode attention of one token over one KV head's paged cache, one key split per workgroup (the
-// stage launches and the row-block launches share it, so both compute the same bits).
+// Decode attention of one token over one KV head's paged cache, one key split per workgroup. The stage
+// launches, the row blocks in vector form and the ragged calls in vector form share it, so they compute
+// the same bits; the second half of the file is the form for rows that share a cache, on matrix cores.
 //
 // The token at position pos0 attends to keys 0..pos0 of its own layer (Section 3.1: each stage's
 // token reads the cache of the layer it is on). Its G query heads share KV head g (grouped-query
@@ -470,7 +471,7 @@ constexpr size_t attn_mfma_lds(int M) {
   return (qp + vt > o ? qp + vt : o) + (size_t)(kWG / 64) * 64 * 4;
 }
 
-// Rows at consecutive positions (a row block, or one stage's token).
+// Rows at consecutive positions (a row block).
 struct LimPos {
   int pos0;
   __device__ __forceinline__ int operator()(int r) const { return pos0 + r; }

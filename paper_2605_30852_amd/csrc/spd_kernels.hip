@@ -876,7 +876,7 @@ __device__ __forceinline__ int pdm_token(const Ctx& C, int i) { return C.pdm_V >
 // ------------------------------------------------------------------------------- attention
 // Decode attention of a stage launch. Grid: x = key split, y = KV head, z = stage of the launch.
 // The page of this thread's first key and the device state are requested together at entry; the
-// split itself is attn_split (shared with the persistent step kernel).
+// split itself is attn_split.
 // GP: head slots of the split (4 or 8), or 0 to choose from C.G at run time.
 template <typename KVT, int DH, int GP = 0>
 __device__ __forceinline__ void attn_part(const Ctx& C, int s, int slot, const KVT* kv, int set, int g, int split) {
@@ -1346,7 +1346,7 @@ static inline size_t stream_lds(int K) {
   return (size_t)(K + BLK - 1) / BLK * BLK * sizeof(float);
 }
 
-// Stage launches (r.kind == 0); row blocks go through rows_layer.
+// Stage launches (r.kind == 0); row blocks go through RowBlocks.
 template <typename WT>
 void Launch<WT>::qkv(const Ctx& c, const Rows& r, void* s) {
   const int np = (c.hq + 2 * c.hkv) * (c.dh / 2);

@@ -1,15 +1,15 @@
 // Row blocks of bf16 models on matrix cores, the prefill's chunks of up to kPrefillRows prompt rows and
-// the draft module's in-flight rows: the launchers of spd_prefill.hip and the scratch they use.
+// (where the stages do not hide its vector form) the draft module's in-flight rows: the launchers of spd_prefill.hip and the scratch they use.
 // Internal; not part of the C ABI.
 #pragma once
 #include "spd_dev.h"
 
 namespace spd {
 
-// Prompt rows of one chunk: 2048 where their scratch stays within kPrefillBytes, else fewer, but at least
-// 1024 (4B class: 1024 rows, 156 MB). A layer's weights are read once per chunk, which at 1024 rows is far
-// below the matrix cores' time; narrow models need the rows to fill 256 CUs (1024 wide, 6000 tokens: 36.3 ms
-// at 2048 rows, 44.7 ms at 1024).
+// Prompt rows of one chunk: 2048 where their scratch stays within kPrefillBytes, else fewer, but never fewer
+// than 1024, whatever that takes (4B class: 1024 rows, 149 MB; 9B class: 192 MB; more where a model is wider). A
+// layer's weights are read once per chunk, which at 1024 rows is far below the matrix cores' time; narrow models
+// need the rows to fill 256 CUs (1024 wide, 6000 tokens: 36.3 ms at 2048 rows, 44.7 ms at 1024).
 constexpr int kPrefillRows = 2048, kPrefillMinRows = 1024;
 constexpr size_t kPrefillBytes = (size_t)160 << 20;
 constexpr int kPrefillMaxSplit = 16;  // K splits of one projection

@@ -219,11 +219,11 @@ __device__ __forceinline__ const uint16_t* weight_row(const GemmArgs& G, int n0,
 // and 1.1e-6 at 9728, against 1.3e-7 and 2.3e-7 for the 64-lane fp32 GEMV and 1.3e-7 and 2.3e-7 (less
 // with K splits) this way, at the same speed.
 //
-// Bound: MFMA issue beside LDS reads (three planes of A against one of W). A workgroup of eight waves
-// over 128 x 256 shares each A tile between four waves: the 4B-class projections of 1501 rows take
-// 434 us (gate/up, 345 TFLOP/s, 1034 of MFMA), 87 (O-proj) and 209 (down), against 510, 103 and 236 for
-// four waves over 128 x 128 twice per CU; a large bf16 library product reaches 1375 TFLOP/s on the same
-// card. Three and four buffers were slower than two (457 to 479 us for gate/up).
+// Bound: LDS reads beside MFMA issue (three planes of A against one of W: a 64 x 64 wave tile reads 16 operands
+// per 24 MFMAs). A workgroup of eight waves over 128 x 256 shares each A tile between four waves: the 4B-class
+// projections of 1501 rows in one chunk took 434 us (gate/up, 345 TFLOP/s of products, 1034 of MFMA), 87 (O-proj)
+// and 209 (down), against 510, 103 and 236 for four waves over 128 x 128 twice per CU; a large bf16 library product
+// reaches 1375 TFLOP/s on the same card. Three and four buffers were slower than two (457 to 479 us for gate/up).
 //
 // Workgroup b runs on XCD b % 8: each XCD takes a contiguous range of the tiles, rows fastest, so the
 // row tiles that share a weight tile share an L2.

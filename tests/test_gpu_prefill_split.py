@@ -1,8 +1,9 @@
-"""GPU lockstep against the oracle for shapes whose prefill chunks take the K-split row GEMV: eight
-prompt rows of the down projection's input (an FFN of 2304) do not fit the row GEMV's LDS budget at
-full width, so each workgroup stages 1024-input chunks (here 1024, 1024 and a ragged 256) and the
-column's last workgroup adds the chunks in order and runs the epilogue. Both weight types (fp32 and
-bf16), a prompt of five full 8-row chunks and a ragged tail, rejections and natural drafts."""
+"""GPU lockstep against the oracle for shapes with an FFN of 2304, wide enough that a prompt's down projection
+is cut along its inputs: in fp32 models eight prompt rows of 2304 inputs do not fit the row GEMV's LDS budget at
+full width, so each workgroup stages 1024-input chunks (here 1024, 1024 and a ragged 256) and the column's last
+workgroup adds the chunks in order and runs the epilogue; in bf16 models the matrix-core GEMM takes K splits,
+whose partial sums the next norm folds. A prompt of five full 8-row chunks and a ragged tail, rejections and
+natural drafts."""
 import sys
 
 import pytest
