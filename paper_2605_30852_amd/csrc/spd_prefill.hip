@@ -219,11 +219,14 @@ __device__ __forceinline__ const uint16_t* weight_row(const GemmArgs& G, int n0,
 // and 1.1e-6 at 9728, against 1.3e-7 and 2.3e-7 for the 64-lane fp32 GEMV and 1.3e-7 and 2.3e-7 (less
 // with K splits) this way, at the same speed.
 //
-// Bound: LDS reads beside MFMA issue (three planes of A against one of W: a 64 x 64 wave tile reads 16 operands
-// per 24 MFMAs). A workgroup of eight waves over 128 x 256 shares each A tile between four waves: the 4B-class
-// projections of 1501 rows in one chunk took 434 us (gate/up, 345 TFLOP/s of products, 1034 of MFMA), 87 (O-proj)
-// and 209 (down), against 510, 103 and 236 for four waves over 128 x 128 twice per CU; a large bf16 library product
-// reaches 1375 TFLOP/s on the same card. Three and four buffers were slower than two (457 to 479 us for gate/up).
+// Bound: the chain from LDS to MFMA between barriers (three planes of A against one of W: a 64 x 64 wave tile
+// reads 16 operands per 24 MFMAs), then the last round of workgroups. Counters at 768 rows of the 4B class: the
+// matrix cores run half of a busy CU's cycles, the LDS a third (half of that bank conflicts), and the CUs are busy
+// 0.82 (gate/up), 0.73 (O-proj, down) and 0.50 (QKV) of a launch. A workgroup of eight waves over 128 x 256 shares
+// each A tile between four waves: the 4B-class projections of 1501 rows in one chunk took 434 us (gate/up, 345
+// TFLOP/s of products, 1034 of MFMA), 87 (O-proj) and 209 (down), against 510, 103 and 236 for four waves over
+// 128 x 128 twice per CU; a large bf16 library product reaches 1375 TFLOP/s on the same card. Three and four buffers
+// were slower than two (457 to 479 us for gate/up).
 //
 // Workgroup b runs on XCD b % 8: each XCD takes a contiguous range of the tiles, rows fastest, so the
 // row tiles that share a weight tile share an L2.
@@ -582,10 +585,10 @@ __global__ __launch_bounds__(kWG) void k_pdm_attn_merge(Ctx C, Planes out) {
 // A workgroup's rows share its key tiles, so 0 * v of a value past a row's own position, or 0 * k of a query
 // plane, makes NaN of a row whose own keys and values do not: a query that ends as NaN is computed again over
 // its own keys by plain FMAs (attn_query_plain).
-// Bound: MFMA (48 per 32 keys) beside the softmax's vector work. A layer of the 4B class takes 37 us for 384
-// rows and 102 + 60 us for the chunks of 768 and 733 rows of 1501; the wide model's chunks of 2048, 2048 and
-// 1904 rows 134, 249 and 356 us. With the page of each tile read where it is used, behind the keys in flight,
-// they took 1.3 to 1.5 times as long.
+// Bound: MFMA (48 per 32 keys, a quarter of a busy CU's cycles) beside the softmax's vector work, and CUs without a
+// workgroup (768 rows of the 4B class are 192). A layer of the 4B class takes 37 us for 384 rows and 59 + 103 us for
+// the chunks of 768 and 733 rows of 1501; the wide model's chunks of 2048, 2048 and 1904 rows 134, 249 and 356 us.
+// With the page of each tile read where it is used, behind the keys in flight, they took 1.3 to 1.5 times as long.
 struct AttnArgs {
   const float* q;
   Planes out;                 // [M][Hq*dh]
