@@ -586,8 +586,8 @@ __global__ __launch_bounds__(kWG) void k_pdm_attn_merge(Ctx C, Planes out) {
 // plane, makes NaN of a row whose own keys and values do not: a query that ends as NaN is computed again over
 // its own keys by plain FMAs (attn_query_plain).
 // Bound: MFMA (48 per 32 keys, a quarter of a busy CU's cycles) beside the softmax's vector work, and CUs without a
-// workgroup (768 rows of the 4B class are 192). A layer of the 4B class takes 37 us for 384 rows and 59 + 103 us for
-// the chunks of 768 and 733 rows of 1501; the wide model's chunks of 2048, 2048 and 1904 rows 134, 249 and 356 us.
+// workgroup (768 rows of the 4B class are 192). A layer of the 4B class takes 37 us for 384 rows and 60 + 102 us for
+// the chunks of 768 and 733 rows of 1501; the wide model's chunks of 2048, 2048 and 1904 rows 131, 243 and 352 us.
 // With the page of each tile read where it is used, behind the keys in flight, they took 1.3 to 1.5 times as long.
 struct AttnArgs {
   const float* q;
@@ -605,7 +605,9 @@ struct AttnArgs {
 //   keys       one accumulator       256-key segments      fp32 MFMA, splits of 128 keys
 //   1501       1.6e-7 (3.8e-7)       1.2e-7 (3.4e-7)       1.3e-7 (5.7e-7)
 //   6000       2.8e-7 (5.2e-7)       1.3e-7 (3.9e-7)       1.4e-7 (6.4e-7)
-// 512-key segments are at 1.6e-7 at 6000 keys. expf and a scale without log2(e) change none of these figures.
+// The segments cost the wide model's three chunks of 6000 tokens a tenth of their attention (118, 219 and 317 us
+// without them; eight loads of the earlier sums at once, as four took longer and sixteen spill). 512-key segments are
+// at 1.6e-7 at 6000 keys. expf and a scale without log2(e) change none of these figures.
 constexpr int kPfSeg = 4;
 
 template <int DH>
@@ -703,34 +705,33 @@ __global__ __launch_bounds__(kWG, 2) void k_pf_attn(AttnArgs A) {
   // the earlier segments' sums join this one's; keep: the result goes back and this segment's sums start over
   auto fold = [&](bool first, bool keep) {
     float4* tot = A.tot + (((size_t)blockIdx.y * gridDim.x + blockIdx.x) * (kWG / 64) + wu) * ((NT * 4 + 1) * 64) + lane;
-    float al = 0.f;
     if (!first) {
       const float2 ml = *reinterpret_cast<const float2*>(tot + NT * 4 * 64);
-      al = __builtin_amdgcn_exp2f(ml.x - m_run);
+      const float al = __builtin_amdgcn_exp2f(ml.x - m_run);
       l_run = fmaf(ml.y, al, l_run);
-    }
 #pragma unroll
-    for (int tt = 0; tt < NT; tt++) {
-      if (!first) {
-        float4 x[4];
+      for (int b = 0; b < NT * 4; b += 8) {
+        float4 x[8];  // a round trip for eight of them
 #pragma unroll
-        for (int i = 0; i < 4; i++) x[i] = tot[(tt * 4 + i) * 64];
+        for (int i = 0; i < 8; i++) x[i] = tot[(b + i) * 64];
 #pragma unroll
-        for (int i = 0; i < 4; i++) {
-          o[tt][4 * i] = fmaf(x[i].x, al, o[tt][4 * i]);
-          o[tt][4 * i + 1] = fmaf(x[i].y, al, o[tt][4 * i + 1]);
-          o[tt][4 * i + 2] = fmaf(x[i].z, al, o[tt][4 * i + 2]);
-          o[tt][4 * i + 3] = fmaf(x[i].w, al, o[tt][4 * i + 3]);
+        for (int i = 0; i < 8; i++) {
+          const int tt = (b + i) / 4, v = (b + i) % 4 * 4;
+          o[tt][v] = fmaf(x[i].x, al, o[tt][v]);
+          o[tt][v + 1] = fmaf(x[i].y, al, o[tt][v + 1]);
+          o[tt][v + 2] = fmaf(x[i].z, al, o[tt][v + 2]);
+          o[tt][v + 3] = fmaf(x[i].w, al, o[tt][v + 3]);
         }
       }
-      if (keep) {
+    }
+    if (keep) {
+#pragma unroll
+      for (int tt = 0; tt < NT; tt++) {
 #pragma unroll
         for (int i = 0; i < 4; i++)
           tot[(tt * 4 + i) * 64] = make_float4(o[tt][4 * i], o[tt][4 * i + 1], o[tt][4 * i + 2], o[tt][4 * i + 3]);
         o[tt] = (f32x16)(0.f);
       }
-    }
-    if (keep) {
       *reinterpret_cast<float2*>(tot + NT * 4 * 64) = make_float2(m_run, l_run);
       l_run = 0.f;
     }
@@ -812,8 +813,8 @@ __global__ __launch_bounds__(kWG, 2) void k_pf_attn(AttnArgs A) {
       }
       l_run += ps + __shfl_xor(ps, 32, 64);
     }
-    if (more && (t + 1) % kPfSeg == 0) fold(t + 1 == kPfSeg, true);
     if (more) store_v(buf ^ 1, t + 1);
+    if (more && (t + 1) % kPfSeg == 0) fold(t + 1 == kPfSeg, true);
   }
   if (tiles > kPfSeg) fold(false, false);
   bool nan = l_run != l_run;
