@@ -586,8 +586,8 @@ __global__ __launch_bounds__(kWG) void k_pdm_attn_merge(Ctx C, Planes out) {
 // plane, makes NaN of a row whose own keys and values do not: a query that ends as NaN is computed again over
 // its own keys by plain FMAs (attn_query_plain).
 // Bound: MFMA (48 per 32 keys, a quarter of a busy CU's cycles) beside the softmax's vector work, and CUs without a
-// workgroup (768 rows of the 4B class are 192). A layer of the 4B class takes 37 us for 384 rows and 60 + 102 us for
-// the chunks of 768 and 733 rows of 1501; the wide model's chunks of 2048, 2048 and 1904 rows 131, 243 and 352 us.
+// workgroup (768 rows of the 4B class are 192). A layer of the 4B class takes 35 us for 384 rows and 60 + 100 us for
+// the chunks of 768 and 733 rows of 1501; the wide model's chunks of 2048, 2048 and 1904 rows 131, 243 and 349 us.
 // With the page of each tile read where it is used, behind the keys in flight, they took 1.3 to 1.5 times as long.
 struct AttnArgs {
   const float* q;
@@ -600,15 +600,17 @@ struct AttnArgs {
 };
 
 // Key tiles of a segment, after which the sums restart from zero and the segment's join those before it, kept
-// in global memory (the registers hold one set). One accumulator over the whole prompt rounds every product's
-// sum at the running total's magnitude; relative error on flat scores (and at scores of deviation 1.5):
-//   keys       one accumulator       256-key segments      fp32 MFMA, splits of 128 keys
-//   1501       1.6e-7 (3.8e-7)       1.2e-7 (3.4e-7)       1.3e-7 (5.7e-7)
-//   6000       2.8e-7 (5.2e-7)       1.3e-7 (3.9e-7)       1.4e-7 (6.4e-7)
-// The segments cost the wide model's three chunks of 6000 tokens a tenth of their attention (118, 219 and 317 us
-// without them; eight loads of the earlier sums at once, as four took longer and sixteen spill). 512-key segments are
-// at 1.6e-7 at 6000 keys. expf and a scale without log2(e) change none of these figures.
-constexpr int kPfSeg = 4;
+// in global memory (the registers hold one set); up to kPfSegLast more tiles at the end make no segment of their own.
+// One accumulator over the whole prompt rounds every product's sum at the running total's magnitude; relative error
+// on flat scores (and at scores of deviation 1.5):
+//   keys       one accumulator       256-key segments      fp32 MFMA, splits of 64 (6000: 128) keys
+//    760       1.3e-7 (3.3e-7)       1.1e-7 (3.2e-7)       1.2e-7 (5.3e-7)
+//   1501       1.6e-7 (3.8e-7)       1.2e-7 (3.5e-7)       1.3e-7 (5.7e-7)
+//   6000       2.8e-7 (5.2e-7)       1.4e-7 (3.9e-7)       1.4e-7 (6.4e-7)
+// 384-key segments are at 1.5e-7 at 6000 keys. A segment costs 1.5 us, half of it the round trip of the earlier sums
+// (eight loads at once; four took longer and sixteen spill): the wide model's three chunks of 6000 tokens took 118,
+// 219 and 317 us a layer with one accumulator. expf and a scale without log2(e) change none of the errors.
+constexpr int kPfSeg = 4, kPfSegLast = 2;
 
 template <int DH>
 __global__ __launch_bounds__(kWG, 2) void k_pf_attn(AttnArgs A) {
@@ -658,6 +660,7 @@ __global__ __launch_bounds__(kWG, 2) void k_pf_attn(AttnArgs A) {
   // wait for a page ever waits for keys or values in flight.
   auto pages = [&](int t) { return A.page_table[min(t * (KT / PAGE) + (lane & 3), A.max_pages - 1)]; };
   const int wu = __builtin_amdgcn_readfirstlane(w);
+  const int wlast = A.pos0 + min(row0 + (wu * 32 + 31) / G, A.M - 1);  // last key of the wave's last row
   auto issue_k = [&](int buf, int pg) {
 #pragma unroll
     for (int i = 0; i < KPT; i++) {
@@ -755,6 +758,7 @@ __global__ __launch_bounds__(kWG, 2) void k_pf_attn(AttnArgs A) {
     const char* vt = kt + KBUF;
 #pragma unroll UB
     for (int b = 0; b < 2; b++) {  // 32 keys at a time
+      if (t * KT + b * 32 > wlast) continue;  // past every row of the wave
       const int key = b * 32 + col;
       f32x16 s;
 #pragma unroll
@@ -814,9 +818,9 @@ __global__ __launch_bounds__(kWG, 2) void k_pf_attn(AttnArgs A) {
       l_run += ps + __shfl_xor(ps, 32, 64);
     }
     if (more) store_v(buf ^ 1, t + 1);
-    if (more && (t + 1) % kPfSeg == 0) fold(t + 1 == kPfSeg, true);
+    if (t + 1 + kPfSegLast < tiles && (t + 1) % kPfSeg == 0) fold(t + 1 == kPfSeg, true);
   }
-  if (tiles > kPfSeg) fold(false, false);
+  if (tiles > kPfSeg + kPfSegLast) fold(false, false);
   bool nan = l_run != l_run;
 #pragma unroll
   for (int tt = 0; tt < NT; tt++)
