@@ -7,8 +7,8 @@ projection and a head that copy. The stored keys and values are read back, so th
 kernel's own inputs; values of 1024 make the copied residual, the final norm and the logits cost no more than
 some 6e-8 of the result.
 
-Bound: 2e-7 relative (2-norm). Restarting sums every 256 keys measures 0.9e-7 to 1.4e-7 on this kind of input,
-one accumulator over 6000 keys 2.8e-7."""
+Bound: 2e-7 relative (2-norm). Sums that restart every 256 keys measure 1.0e-7 to 1.7e-7 here, one accumulator 1.6e-7 at 300
+keys and 6.3e-7 at 6000."""
 import sys
 
 import numpy as np
